@@ -61,13 +61,13 @@ constexpr int kFromNext = 0x130;
 template <int CTRL>
 __device__ __forceinline__ double lane_shift(double x) {
   const long long bits = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(bits & 0xffffffffll), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), CTRL, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(bits & 0xffffffffll), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 template <int CTRL>
 __device__ __forceinline__ float lane_shift(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
 template <int DIR, int D, typename Real>
@@ -310,7 +310,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   // they carry Kapila's K of the cell, (alpha_1 + K, alpha_2 - K)
   Real alpha_cell[2] = {Real(0), Real(0)};
   if (centre_ok) {
-    const Real eps = Real(pm.eps);
+    const WenoK<Real> K = weno_consts(Real(pm.eps));
     // non-uniform grid: the table entry of centre c along this axis
     const long long nst = (long long)nd + 6;
     const Real* cf = nullptr;
@@ -328,9 +328,9 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
       const Real f3 = sh[lds_index<DIR, D, Real>(v, a + 3, b)];
       const Real f4 = sh[lds_index<DIR, D, Real>(v, a + 4, b)];
       if constexpr (WV == kWvNonUniform)
-        weno5_nu(f0, f1, f2, f3, f4, eps, cf, nst, WLc[v], WRc[v]);
+        weno5_nu(f0, f1, f2, f3, f4, K.eps, cf, nst, WLc[v], WRc[v]);
       else
-        weno5<WV>(f0, f1, f2, f3, f4, eps, WLc[v], WRc[v]);
+        weno5<WV>(f0, f1, f2, f3, f4, K, WLc[v], WRc[v]);
     }
     if constexpr (NF == 2) {
       alpha_cell[0] = sh[lds_index<DIR, D, Real>(R::ALPHA, a + 2, b)];

@@ -205,6 +205,7 @@ __device__ __forceinline__ void face_tile(const Params pm, const double* __restr
     cfa = pm.nu[DIR] + (f - 1 + 3);
     cfb = pm.nu[DIR] + (f + 3);
   }
+  const WenoK<double> K = weno_consts(pm.eps);
   double WL[NEQ], WR[NEQ];
 #pragma unroll
   for (int v = 0; v < NEQ; ++v) {
@@ -213,8 +214,8 @@ __device__ __forceinline__ void face_tile(const Params pm, const double* __restr
       weno5_nu(Ws(0, v), Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), pm.eps, cfa, nst, l, t);
       weno5_nu(Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), Ws(5, v), pm.eps, cfb, nst, t, r);
     } else {
-      weno5<WV>(Ws(0, v), Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), pm.eps, l, t);
-      weno5<WV>(Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), Ws(5, v), pm.eps, t, r);
+      weno5<WV>(Ws(0, v), Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), K, l, t);
+      weno5<WV>(Ws(1, v), Ws(2, v), Ws(3, v), Ws(4, v), Ws(5, v), K, t, r);
     }
     WL[v] = l;
     WR[v] = r;
