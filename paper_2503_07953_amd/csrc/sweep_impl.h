@@ -2,7 +2,8 @@
 // launch sequence, templated on the reconstruction variant WV.  Each
 // sweep_wv*.hip translation unit instantiates one variant (so that the
 // variants compile in parallel); sweep.hip dispatches among them.
-// One fused pass per grid axis of the five-equation RHS.
+// One fused pass per grid axis of the five-equation RHS (the y and x axes of
+// large 3D grids go in one marching pass instead, march_impl.h).
 //
 // A pass over axis DIR does, for a tile of cells, in one kernel:
 //   (a) load the conservative state of the tile plus three ghost/halo cells on
@@ -34,6 +35,8 @@
 
 #include "device.h"
 #include "internal.h"
+#include "lanes.h"
+#include "march_impl.h"
 
 namespace mfc {
 
@@ -51,23 +54,6 @@ __device__ __forceinline__ void st_acc(Real v, Real* p) {
     __builtin_nontemporal_store(v, p);
   else
     *p = v;
-}
-
-// Exchange between adjacent lanes of a wave (DPP wave_shr:1 / wave_shl:1):
-// lane i receives lane i-1's value (kFromPrev) or lane i+1's (kFromNext); the
-// lane at the end with no source receives 0.  Called with every lane active.
-constexpr int kFromPrev = 0x138;
-constexpr int kFromNext = 0x130;
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double x) {
-  const long long bits = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(bits & 0xffffffffll), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), CTRL, 0xf, 0xf, true);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
 template <int DIR, int D, typename Real>
@@ -556,9 +542,28 @@ static long long first_pass_blocks(const int* n) {
     return bx * n[1] * ((n[2] + TL::OUT - 1) / TL::OUT);
 }
 
-// All axes of one RHS evaluation, z (or y) first and x last.  final_step: the
-// x pass combines into qout.  sig (2D / 3D): the first pass also forms the
-// signal-speed block maxima and dt is formed before the x pass reads it.
+// The first axis pass (z in 3D, y in 2D).  sig: it also forms the signal-speed
+// block maxima, and dt is formed from them.
+template <int NF, int D, typename Real, int WV, int RS>
+static hipError_t launch_first(const Params& pm, const Real* qk, Real* acc, const Real* qn, Real* qout, StageArgs st,
+                               int* flag, hipStream_t s, PassTimer* tm, const SignalFuse* sig) {
+  constexpr int FIRST = D - 1;
+  if (!sig) return launch_one<NF, D, FIRST, Real, MODE_WRITE, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+  st.sig_partial = sig->partial;
+  hipError_t e = launch_one<NF, D, FIRST, Real, MODE_WRITE | MODE_SIGNAL, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+  if (e != hipSuccess) return e;
+  if (tm) tm->begin(KIND_SIGNAL, s);
+  e = launch_finalize_dt(sig->partial, (int)first_pass_blocks<D, Real>(pm.n), sig->cfl, sig->t_remaining, sig->smax_out,
+                         sig->dt_out, sig->dt_user, s);
+  if (tm) tm->end(KIND_SIGNAL, s);
+  return e;
+}
+
+// All axes of one RHS evaluation.  final_step: the last pass combines into
+// qout.  sig (2D / 3D): the first pass also forms the signal-speed block
+// maxima and dt is formed before the last pass reads it.  From the highest axis
+// down, each in a pass of its own; the y and x axes of large 3D grids in one
+// marching pass (march_pays).
 template <int NF, int D, typename Real, int WV, int RS>
 static hipError_t launch_rhs_t(const Params& pm, const Real* qk, Real* acc, const Real* qn, Real* qout,
                                StageArgs st, bool final_step, int* flag, hipStream_t s, PassTimer* tm,
@@ -571,21 +576,15 @@ static hipError_t launch_rhs_t(const Params& pm, const Real* qk, Real* acc, cons
     else
       e = launch_one<NF, D, 0, Real, MODE_WRITE, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
   } else {
-    constexpr int FIRST = D - 1;
-    if (sig) {
-      StageArgs s1 = st;
-      s1.sig_partial = sig->partial;
-      e = launch_one<NF, D, FIRST, Real, MODE_WRITE | MODE_SIGNAL, WV, RS>(pm, qk, acc, qn, qout, s1, flag, s, tm);
-      if (e != hipSuccess) return e;
-      if (tm) tm->begin(KIND_SIGNAL, s);
-      e = launch_finalize_dt(sig->partial, (int)first_pass_blocks<D, Real>(pm.n), sig->cfl, sig->t_remaining,
-                             sig->smax_out, sig->dt_out, sig->dt_user, s);
-      if (tm) tm->end(KIND_SIGNAL, s);
-    } else {
-      e = launch_one<NF, D, FIRST, Real, MODE_WRITE, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
-    }
+    e = launch_first<NF, D, Real, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm, sig);
     if (e != hipSuccess) return e;
     if constexpr (D == 3) {
+      if constexpr (kMarchVariant<WV>) {
+        if (march_pays<Real>(pm)) {
+          if (final_step) return launch_march<NF, Real, MODE_ACC | MODE_STEP, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+          return launch_march<NF, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+        }
+      }
       e = launch_one<NF, D, 1, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
       if (e != hipSuccess) return e;
     }
