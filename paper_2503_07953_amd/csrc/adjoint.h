@@ -10,6 +10,9 @@
 
 namespace mfc {
 
+// Reconstruction variant with tabulated coefficients (non-uniform grids).
+constexpr int kWvTable = 4;
+
 // cons->prim adjoint: given wbar (cotangent of alpha_i rho_i, u_d, p, alpha_i)
 // at the state U, accumulate Ubar.  Forward: rho = sum alpha_i rho_i,
 // u = m/rho, p = (E - |m|^2/(2 rho) - Pi)/Gamma, Gamma/Pi linear in alpha.
@@ -54,6 +57,38 @@ __host__ __device__ __forceinline__ void cons_to_prim_vjp(const Params& pm, cons
   }
 }
 
+// The same from the primitive state W (u and p are at hand; no inversion).
+template <int NF, int D>
+__host__ __device__ __forceinline__ void cons_to_prim_vjp_at_prim(const Params& pm, const double* W, const double* wbar,
+                                                                  double* Ubar) {
+  using R = Rows<NF, D>;
+  double rho = W[0];
+  if constexpr (NF == 2) rho = W[0] + W[1];
+  const double rinv = fast_rcp(rho);
+  double Gam, Pi;
+  if constexpr (NF == 2)
+    mixture<NF, double>(pm, W[R::ALPHA], W[R::ALPHA + 1], Gam, Pi);
+  else
+    mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
+  const double gi = fast_rcp(Gam);
+  const double Eb = wbar[R::E] * gi;
+  double rhob = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const double u = W[R::MOM + d];
+    const double ub = wbar[R::MOM + d] * rinv;
+    Ubar[R::MOM + d] = ub - Eb * u;
+    rhob += (0.5 * Eb * u - ub) * u;
+  }
+  Ubar[R::E] = Eb;
+#pragma unroll
+  for (int i = 0; i < NF; ++i) Ubar[i] = wbar[i] + rhob;
+  if constexpr (NF == 2) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) Ubar[R::ALPHA + j] = wbar[R::ALPHA + j] - Eb * (W[R::E] * pm.G[j] + pm.P[j]);
+  }
+}
+
 // prim->cons adjoint: given qbar at the primitive state W, accumulate Wbar.
 // Forward: m = rho u, E = Gamma p + Pi + rho |u|^2 / 2.
 template <int NF, int D>
@@ -89,56 +124,46 @@ __host__ __device__ __forceinline__ void prim_to_cons_vjp(const Params& pm, cons
   }
 }
 
-// Adjoint of the left-biased WENO5-JS value at i+1/2 from f = (a, b, c, d, e),
-// in the difference form of the forward: with D0..D3 the consecutive
-// differences, y = c + sum_k w_k l_k / 6, w_k = d_k s_k^-2 / sum_j d_j s_j^-2,
-// s_k = 4 (eps + beta_k) (a common factor the weights ignore), and
-// l_0 = 5D1 - 2D0, l_1 = D1 + 2D2, l_2 = 4D2 - D3 six times the candidate
-// corrections.  One refined reciprocal of N * s0 s1 s2 with
-// N = sum_k d_k prod_{j != k} s_j^2 gives both 1/N (the weights) and
-// 1/(s0 s1 s2) (the indicator derivatives dy/ds_k = -2 w_k (l_k/6 - (y - c))/s_k).
-// Accumulates g[0..4].
-__host__ __device__ __forceinline__ void weno_left_vjp(double a, double b, double c, double d, double e,
-                                                       double eps, double gy, double* g) {
-  const double D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
-  const double u0 = D1 - D0, v0 = 3.0 * D1 - D0;
-  const double u1 = D2 - D1, v1 = D1 + D2;
-  const double u2 = D3 - D2, v2 = D3 - 3.0 * D2;
-  const double e4 = 4.0 * eps;
-  const double s0 = e4 + ((13.0 / 3.0) * u0 * u0 + v0 * v0);
-  const double s1 = e4 + ((13.0 / 3.0) * u1 * u1 + v1 * v1);
-  const double s2 = e4 + ((13.0 / 3.0) * u2 * u2 + v2 * v2);
-  const double m0 = s1 * s2, m1 = s0 * s2, m2 = s0 * s1;   // prod_{j != k} s_j
-  const double n0 = 0.1 * (m0 * m0), n1 = 0.6 * (m1 * m1), n2 = 0.3 * (m2 * m2);
-  const double N = n0 + n1 + n2;
-  const double P = s0 * m0;
-  const double inv = fast_rcp(N * P);
-  const double rN = P * inv;    // 1/N
-  const double rP = N * inv;    // 1/(s0 s1 s2)
-  const double w0 = n0 * rN, w1 = n1 * rN, w2 = n2 * rN;
-  const double l0 = 5.0 * D1 - 2.0 * D0, l1 = D1 + 2.0 * D2, l2 = 4.0 * D2 - D3;
-  const double k6 = 1.0 / 6.0;
-  const double dy = (w0 * l0 + w1 * l1 + w2 * l2) * k6;
-  // cotangents of l_k and s_k
-  const double gk = gy * k6;
-  const double gl0 = gk * w0, gl1 = gk * w1, gl2 = gk * w2;
-  const double g2 = -2.0 * gy * rP;
-  const double gs0 = g2 * w0 * (l0 * k6 - dy) * m0;
-  const double gs1 = g2 * w1 * (l1 * k6 - dy) * m1;
-  const double gs2 = g2 * w2 * (l2 * k6 - dy) * m2;
-  const double gu0 = gs0 * (26.0 / 3.0) * u0, gv0 = gs0 * 2.0 * v0;
-  const double gu1 = gs1 * (26.0 / 3.0) * u1, gv1 = gs1 * 2.0 * v1;
-  const double gu2 = gs2 * (26.0 / 3.0) * u2, gv2 = gs2 * 2.0 * v2;
-  // back to the differences, then to the five values
-  const double gD0 = -2.0 * gl0 - gu0 - gv0;
-  const double gD1 = 5.0 * gl0 + gl1 + gu0 + 3.0 * gv0 - gu1 + gv1;
-  const double gD2 = 2.0 * gl1 + 4.0 * gl2 + gu1 + gv1 - gu2 - 3.0 * gv2;
-  const double gD3 = -gl2 + gu2 + gv2;
-  g[0] -= gD0;
-  g[1] += gD0 - gD1;
-  g[2] += gy + gD1 - gD2;
-  g[3] += gD2 - gD3;
-  g[4] += gD3;
+// Adjoints of one reconstruction centre: with gL the cotangent of the left-
+// biased value at i+1/2 and gR that of the right-biased value at i-1/2, the
+// cotangents gD[0..3] of the four consecutive differences D_k of the stencil's
+// five values; the centre value itself also collects gL + gR (both values are
+// the centre plus a function of the differences).
+//
+// WENO5-JS, in the forms of weno5_js: per side the value is c +- (h - t)/3 with
+// t the weighted third differences over their normalization, t_L = b_0 A + 3/2
+// b_2 B with weights b_k = a_k/n_L (b_0 + 6 b_1 + 3 b_2 = 1), t_R its mirror
+// image.  a_k ~ s_k^-2, so dt_L/ds_0 = -2 b_0 (A - t_L)/s_0, dt_L/ds_1 = 12 b_1
+// t_L/s_1, dt_L/ds_2 = -2 b_2 (3/2 B - 3 t_L)/s_2; the quadratic forms s_k give
+// the differences.  Both sides share the indicators and their derivatives (the
+// two one-sided adjoints of a face formed them twice).
+__host__ __device__ __forceinline__ void weno_js_centre_vjp(double a, double b, double c, double d, double e,
+                                                            const WenoK<double>& K, double gL, double gR, double* gD) {
+  const double D0 = b - a, D3 = e - d;
+  const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
+  const double D1 = w.D1, D2 = w.D2;
+  const double m0 = w.s1 * w.s2, m1 = w.s0 * w.s2, m2 = w.s0 * w.s1;
+  const double a0 = m0 * m0, a1 = m1 * m1, a2 = m2 * m2;
+  const double dl = K.p3 * a2 + (K.p6 * a1 + a0), dr = K.p3 * a0 + (K.p6 * a1 + a2);
+  const double inv = fast_rcp(dl * dr);
+  const double il = dr * inv, ir = dl * inv;
+  const double rP = fast_rcp(w.s0 * m0);
+  const double l0 = a0 * il, l1 = a1 * il, l2 = a2 * il;
+  const double r0 = a0 * ir, r1 = a1 * ir, r2 = a2 * ir;
+  const double A15 = K.p15 * w.A, B15 = K.p15 * w.B;
+  const double tl = l0 * w.A + l2 * B15, tr = r2 * w.B + r0 * A15;
+  // cotangents: t_L = -gL/3, t_R = gR/3, h_L = gL/3, h_R = -gR/3
+  const double gl = K.third * gL, gr = K.third * gR;
+  const double L0 = gl * l0, L2 = gl * l2, R0 = gr * r0, R2 = gr * r2;
+  const double tl3 = K.p3 * tl, tr3 = K.p3 * tr;
+  const double g0 = 2.0 * (L0 * (w.A - tl) - R0 * (A15 - tr3)) * (m0 * rP);
+  const double g1 = 12.0 * (gr * (r1 * tr) - gl * (l1 * tl)) * (m1 * rP);
+  const double g2 = 2.0 * (L2 * (B15 - tl3) - R2 * (w.B - tr)) * (m2 * rP);
+  const double gA = K.p15 * R0 - L0, gB = R2 - K.p15 * L2;
+  gD[0] = gA + g0 * (2.0 * D0 + K.m275 * D1);
+  gD[1] = (gB - 2.0 * gA) + (0.5 * gl - gr) + (g0 * (5.0 * D1 + K.m275 * D0) + g1 * (2.0 * D1 + K.m125 * D2));
+  gD[2] = (gA - 2.0 * gB) + (gl - 0.5 * gr) + (g2 * (5.0 * D2 + K.m275 * D3) + g1 * (2.0 * D2 + K.m125 * D1));
+  gD[3] = gB + g2 * (2.0 * D3 + K.m275 * D2);
 }
 
 // Adjoint of the left-biased WENO5-Z value (Sec. 4.2.2) in the same difference
@@ -148,9 +173,9 @@ __host__ __device__ __forceinline__ void weno_left_vjp(double a, double b, doubl
 // -G_k d_k tau/s_k^2; of tau, sum_k G_k d_k/s_k, which reaches s_0 and s_2 with
 // the sign of s_0 - s_2 (none at a tie).  One refined reciprocal of
 // Z s_0 s_1 s_2 (Z = A s_0 s_1 s_2) gives 1/Z, 1/A and every 1/s_k.
-// Accumulates g[0..4].
+// Returns the cotangents gD[0..3] of the differences.
 __host__ __device__ __forceinline__ void weno_z_left_vjp(double a, double b, double c, double d, double e,
-                                                         double eps, double gy, double* g) {
+                                                         double eps, double gy, double* gD) {
   const double D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
   const double u0 = D1 - D0, v0 = 3.0 * D1 - D0;
   const double u1 = D2 - D1, v1 = D1 + D2;
@@ -190,11 +215,10 @@ __host__ __device__ __forceinline__ void weno_z_left_vjp(double a, double b, dou
   const double gD1 = 5.0 * gl0 + gl1 + gu0 + 3.0 * gv0 - gu1 + gv1;
   const double gD2 = 2.0 * gl1 + 4.0 * gl2 + gu1 + gv1 - gu2 - 3.0 * gv2;
   const double gD3 = -gl2 + gu2 + gv2;
-  g[0] -= gD0;
-  g[1] += gD0 - gD1;
-  g[2] += gy + gD1 - gD2;
-  g[3] += gD2 - gD3;
-  g[4] += gD3;
+  gD[0] = gD0;
+  gD[1] = gD1;
+  gD[2] = gD2;
+  gD[3] = gD3;
 }
 
 // Adjoint of the left-biased WENO5-M value (mapped JS weights, Sec. 3.2.1).
@@ -203,9 +227,10 @@ __host__ __device__ __forceinline__ void weno_z_left_vjp(double a, double b, dou
 // Cotangents: of h_k, gy (l_k/6 - (y - c)) / sum h; of w_k, that times
 // g_k'(w_k) = (num_k' den_k - num_k (1 - 2 d_k)) / den_k^2 with num_k' =
 // d_k + d_k^2 - 6 d_k w_k + 3 w_k^2; of s_k, -2 w_k (wbar_k - sum_j wbar_j w_j)/s_k
-// (the JS normalization), then as in weno_left_vjp.  Accumulates g[0..4].
+// (the JS normalization), then through s_k = 4 (eps + beta_k) = 13/3 u_k^2 +
+// v_k^2 to the differences.  Returns their cotangents gD[0..3].
 __host__ __device__ __forceinline__ void weno_m_left_vjp(double a, double b, double c, double d, double e,
-                                                         double eps, double gy, double* g) {
+                                                         double eps, double gy, double* gD) {
   const double D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
   const double u0 = D1 - D0, v0 = 3.0 * D1 - D0;
   const double u1 = D2 - D1, v1 = D1 + D2;
@@ -262,19 +287,18 @@ __host__ __device__ __forceinline__ void weno_m_left_vjp(double a, double b, dou
   const double gD1 = 5.0 * gl0 + gl1 + gu0 + 3.0 * gv0 - gu1 + gv1;
   const double gD2 = 2.0 * gl1 + 4.0 * gl2 + gu1 + gv1 - gu2 - 3.0 * gv2;
   const double gD3 = -gl2 + gu2 + gv2;
-  g[0] -= gD0;
-  g[1] += gD0 - gD1;
-  g[2] += gy + gD1 - gD2;
-  g[3] += gD2 - gD3;
-  g[4] += gD3;
+  gD[0] = gD0;
+  gD[1] = gD1;
+  gD[2] = gD2;
+  gD[3] = gD3;
 }
 
 // Adjoint of the left-biased TENO5 value (Sec. 4.2.2): the kept set is decided
 // exactly as in the forward reconstruction and the weights are then constant,
 // so y = c + sum_k w_k l_k / 6 with w_k = d_k delta_k / sum d delta is linear
-// in the differences.  Accumulates g[0..4].
+// in the differences.  Returns their cotangents gD[0..3].
 __host__ __device__ __forceinline__ void teno_left_vjp(double a, double b, double c, double d, double e,
-                                                       double eps, double gy, double* g) {
+                                                       double eps, double gy, double* gD) {
   const double D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
   const double u0 = D1 - D0, v0 = 3.0 * D1 - D0;
   const double u1 = D2 - D1, v1 = D1 + D2;
@@ -299,30 +323,16 @@ __host__ __device__ __forceinline__ void teno_left_vjp(double a, double b, doubl
   const double gD1 = 5.0 * gl0 + gl1;
   const double gD2 = 2.0 * gl1 + 4.0 * gl2;
   const double gD3 = -gl2;
-  g[0] -= gD0;
-  g[1] += gD0 - gD1;
-  g[2] += gy + gD1 - gD2;
-  g[3] += gD2 - gD3;
-  g[4] += gD3;
-}
-
-// Adjoint of one reconstruction centre: gL is the cotangent of the left-biased
-// value at i+1/2, gR of the right-biased value at i-1/2 (the mirror image).
-__host__ __device__ __forceinline__ void weno5_js_vjp(const double* f, double eps, double gL, double gR, double* g) {
-  weno_left_vjp(f[0], f[1], f[2], f[3], f[4], eps, gL, g);
-  double gr[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  weno_left_vjp(f[4], f[3], f[2], f[1], f[0], eps, gR, gr);
-  g[0] += gr[4];
-  g[1] += gr[3];
-  g[2] += gr[2];
-  g[3] += gr[1];
-  g[4] += gr[0];
+  gD[0] = gD0;
+  gD[1] = gD1;
+  gD[2] = gD2;
+  gD[3] = gD3;
 }
 
 // ---------------------------------------------------------------------------
 // Adjoint of the non-uniform WENO5-JS of one centre (weno5_nu): with
 // cotangents gR of the value at the right face and gL of the value at the
-// left face, accumulates g[0..4] of the five cell values.  Forward: per
+// left face, the cotangents gD[0..3] of the four differences.  Forward: per
 // candidate r, m0' = mu0 (D_r, D_{r+1}), m1, m2 linear in the two differences,
 // values f_2 + m0' + m2/4 +- m1/2, indicator beta_r = m1^2 + (13/3) m2^2,
 // weights d_r/(eps + beta_r)^2 normalized per face.  Reverse: the candidate
@@ -330,7 +340,7 @@ __host__ __device__ __forceinline__ void weno5_js_vjp(const double* f, double ep
 // g omega_r (q_r - (y - f_2)) from each face.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void weno_nu_vjp(double a, double b, double c, double d, double e, double eps,
-                                            const double* cf, long long st, double gR, double gL, double* g) {
+                                            const double* cf, long long st, double gR, double gL, double* gD) {
   const double D[4] = {b - a, c - b, d - c, e - d};
   double qr[3], ql[3], beta[3], m1[3], m2[3];
 #pragma unroll
@@ -365,7 +375,7 @@ __device__ __forceinline__ void weno_nu_vjp(double a, double b, double c, double
     cL += wl[r] * ql[r];
   }
   const double sv[3] = {s0, s1, s2};
-  double Db[4] = {0.0, 0.0, 0.0, 0.0};
+  gD[0] = gD[1] = gD[2] = gD[3] = 0.0;
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
     const double qrb = gR * wr[r], qlb = gL * wl[r];
@@ -373,15 +383,37 @@ __device__ __forceinline__ void weno_nu_vjp(double a, double b, double c, double
     const double mu0b = qrb + qlb;
     const double m1b = 0.5 * (qrb - qlb) + 2.0 * m1[r] * bb;
     const double m2b = 0.25 * (qrb + qlb) + (26.0 / 3.0) * m2[r] * bb;
-    Db[r] += cf[(NU_MU0 + 2 * r) * st] * mu0b + cf[(NU_M1 + 2 * r) * st] * m1b + cf[(NU_M2 + 2 * r) * st] * m2b;
-    Db[r + 1] += cf[(NU_MU0 + 2 * r + 1) * st] * mu0b + cf[(NU_M1 + 2 * r + 1) * st] * m1b +
+    gD[r] += cf[(NU_MU0 + 2 * r) * st] * mu0b + cf[(NU_M1 + 2 * r) * st] * m1b + cf[(NU_M2 + 2 * r) * st] * m2b;
+    gD[r + 1] += cf[(NU_MU0 + 2 * r + 1) * st] * mu0b + cf[(NU_M1 + 2 * r + 1) * st] * m1b +
                  cf[(NU_M2 + 2 * r + 1) * st] * m2b;
   }
-  g[2] += gR + gL;
+}
+
+// The adjoint of one centre for a reconstruction variant (gL: value at i+1/2,
+// gR: at i-1/2); cf and st: the centre's entry of the non-uniform table.  The
+// one-sided adjoints of Z, M and TENO5 run on the stencil and on its mirror
+// image, whose differences are -D_3 .. -D_0.
+template <int WV>
+__device__ __forceinline__ void weno_centre_vjp(double a, double b, double c, double d, double e, const WenoK<double>& K,
+                                                const double* cf, long long st, double gL, double gR, double* gD) {
+  if constexpr (WV == kWvTable) {
+    weno_nu_vjp(a, b, c, d, e, K.eps, cf, st, gL, gR, gD);
+  } else if constexpr (WV == 0) {
+    weno_js_centre_vjp(a, b, c, d, e, K, gL, gR, gD);
+  } else {
+    double m[4];
+    if constexpr (WV == 1) {
+      weno_z_left_vjp(a, b, c, d, e, K.eps, gL, gD);
+      weno_z_left_vjp(e, d, c, b, a, K.eps, gR, m);
+    } else if constexpr (WV == 2) {
+      teno_left_vjp(a, b, c, d, e, K.eps, gL, gD);
+      teno_left_vjp(e, d, c, b, a, K.eps, gR, m);
+    } else {
+      weno_m_left_vjp(a, b, c, d, e, K.eps, gL, gD);
+      weno_m_left_vjp(e, d, c, b, a, K.eps, gR, m);
+    }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    g[k + 1] += Db[k];
-    g[k] -= Db[k];
+    for (int k = 0; k < 4; ++k) gD[k] -= m[3 - k];
   }
 }
 

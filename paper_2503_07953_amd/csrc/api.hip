@@ -94,8 +94,7 @@ struct mfc_ctx {
   std::string err;
   EventTimer* timer;  // non-null while timing is enabled
   // adjoint scratch (allocated on the first adjoint call)
-  mfc::VjpScratch vjp;
-  double* vbuf;       // L^T v
+  double* vbuf;       // primitive cotangents, summed over the axes
   double* b1;         // stage cotangents
   double* b2;
   // non-uniform grid (mfc_set_grid): face coordinates per axis (empty:
@@ -119,46 +118,19 @@ int hip_fail(mfc_ctx* c, hipError_t e, const char* where) {
   return MFC_ERR_HIP;
 }
 
-// Per-axis face buffers (all axes in one face launch) are used while their sum
-// stays within this many bytes; larger grids share one buffer across axes.
-constexpr size_t kAllAxesFaceBudget = size_t(8) << 30;
-
 void free_vjp_scratch(mfc_ctx* c) {
-  for (int d = 0; d < 3; ++d) {
-    if (c->vjp.Gd[d]) (void)hipFree(c->vjp.Gd[d]);
-    if (c->vjp.UFd[d]) (void)hipFree(c->vjp.UFd[d]);
-    c->vjp.Gd[d] = c->vjp.UFd[d] = nullptr;
-  }
   void** bufs[] = {(void**)&c->vbuf, (void**)&c->b1, (void**)&c->b2};
   for (void** b : bufs) {
     if (*b) (void)hipFree(*b);
     *b = nullptr;
   }
-  c->vjp.all_axes = false;
 }
 
 int ensure_vjp_scratch(mfc_ctx* c) {
-  if (c->vjp.Gd[0]) return MFC_OK;
-  long long faces[3] = {0, 0, 0}, maxfaces = 0, sumfaces = 0;
-  for (int d = 0; d < c->prob.ndim; ++d) {
-    const long long lines = c->ncell / c->prob.n[d];
-    faces[d] = lines * (c->prob.n[d] + 1);
-    if (faces[d] > maxfaces) maxfaces = faces[d];
-    sumfaces += faces[d];
-  }
-  const size_t per_face = (size_t)(6 * c->neq + 1) * sizeof(double);
-  size_t budget = kAllAxesFaceBudget;
-  if (const char* env = getenv("MFC355_ADJOINT_FACE_BUDGET")) budget = (size_t)strtoull(env, nullptr, 10);
-  const bool all_axes = (size_t)sumfaces * per_face <= budget;
+  if (c->vbuf) return MFC_OK;
   const size_t state = (size_t)c->neq * (size_t)c->ncell * sizeof(double);
-  bool ok = true;
-  for (int d = 0; d < (all_axes ? c->prob.ndim : 1) && ok; ++d) {
-    const long long nf = all_axes ? faces[d] : maxfaces;
-    ok = hipMalloc((void**)&c->vjp.Gd[d], (size_t)6 * c->neq * (size_t)nf * sizeof(double)) == hipSuccess &&
-         hipMalloc((void**)&c->vjp.UFd[d], (size_t)nf * sizeof(double)) == hipSuccess;
-  }
-  ok = ok && hipMalloc((void**)&c->vbuf, state) == hipSuccess && hipMalloc((void**)&c->b1, state) == hipSuccess &&
-       hipMalloc((void**)&c->b2, state) == hipSuccess;
+  const bool ok = hipMalloc((void**)&c->vbuf, state) == hipSuccess && hipMalloc((void**)&c->b1, state) == hipSuccess &&
+                  hipMalloc((void**)&c->b2, state) == hipSuccess;
   if (!ok) {
     // release whatever was obtained, so that a later call retries from scratch
     (void)hipGetLastError();
@@ -166,7 +138,6 @@ int ensure_vjp_scratch(mfc_ctx* c) {
     c->err = "adjoint scratch allocation failed";
     return MFC_ERR_ALLOC;
   }
-  c->vjp.all_axes = all_axes;
   return MFC_OK;
 }
 
@@ -438,7 +409,6 @@ int mfc_create(const mfc_problem* p, mfc_ctx** out) {
   c->scal = c->partial = nullptr;
   c->flag = nullptr;
   c->timer = nullptr;
-  c->vjp = mfc::VjpScratch{{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}, false};
   c->vbuf = c->b1 = c->b2 = nullptr;
   for (int d = 0; d < 3; ++d) {
     c->nu_d[d] = nullptr;
@@ -615,17 +585,11 @@ StepScratch ctx_scratch(mfc_ctx* c) { return StepScratch{c->acc, c->q1, c->q2, c
 hipError_t step_reverse(mfc_ctx* c, const double* qn, const double* q1, const double* q2, double dt,
                         const double* qnp1_bar, double* qn_bar, hipStream_t s) {
   const int nf = c->prob.num_fluids, nd = c->prob.ndim;
-  const long long n = (long long)c->neq * c->ncell;
-  // with every axis gathered in one cell pass the stage combination is applied
-  // there (no separate pass over v = vbuf); otherwise by launch_adj_stage
-  const bool fused = c->vjp.all_axes;
+  // the last pass of each RHS adjoint applies the stage combination itself
   const mfc::StageEpi e3{3, dt, qnp1_bar, c->b2, qn_bar}, e2{2, dt, c->b2, c->b1, qn_bar}, e1{1, dt, c->b1, nullptr, qn_bar};
-  hipError_t e = mfc::launch_rhs_vjp(nf, nd, c->pm, q2, qnp1_bar, c->vbuf, c->vjp, false, s, c->timer, &e3);
-  if (e == hipSuccess && !fused) e = mfc::launch_adj_stage(3, n, dt, qnp1_bar, c->vbuf, c->b2, qn_bar, s);
-  if (e == hipSuccess) e = mfc::launch_rhs_vjp(nf, nd, c->pm, q1, c->b2, c->vbuf, c->vjp, false, s, c->timer, &e2);
-  if (e == hipSuccess && !fused) e = mfc::launch_adj_stage(2, n, dt, c->b2, c->vbuf, c->b1, qn_bar, s);
-  if (e == hipSuccess) e = mfc::launch_rhs_vjp(nf, nd, c->pm, qn, c->b1, c->vbuf, c->vjp, false, s, c->timer, &e1);
-  if (e == hipSuccess && !fused) e = mfc::launch_adj_stage(1, n, dt, c->b1, c->vbuf, nullptr, qn_bar, s);
+  hipError_t e = mfc::launch_rhs_vjp(nf, nd, c->pm, q2, qnp1_bar, nullptr, c->vbuf, false, s, c->timer, &e3);
+  if (e == hipSuccess) e = mfc::launch_rhs_vjp(nf, nd, c->pm, q1, c->b2, nullptr, c->vbuf, false, s, c->timer, &e2);
+  if (e == hipSuccess) e = mfc::launch_rhs_vjp(nf, nd, c->pm, qn, c->b1, nullptr, c->vbuf, false, s, c->timer, &e1);
   return e;
 }
 }  // namespace
@@ -728,7 +692,7 @@ int mfc_rhs_vjp(mfc_ctx* c, const void* q, const void* rhs_bar, void* q_bar, int
   if (q_bar == q || q_bar == rhs_bar) return fail(c, MFC_ERR_ARG, "q_bar aliases an input");
   if ((r = ensure_vjp_scratch(c))) return r;
   hipError_t e = mfc::launch_rhs_vjp(c->prob.num_fluids, c->prob.ndim, c->pm, (const double*)q,
-                                     (const double*)rhs_bar, (double*)q_bar, c->vjp, accumulate != 0,
+                                     (const double*)rhs_bar, (double*)q_bar, c->vbuf, accumulate != 0,
                                      (hipStream_t)stream, c->timer);
   return e == hipSuccess ? MFC_OK : hip_fail(c, e, "rhs_vjp");
 }

@@ -1,6 +1,5 @@
 // vjp.hip -- dispatch of the RHS adjoint over the reconstruction variants
-// (vjp_wv*.hip), and the adjoints of the field conversions and of the SSP-RK3
-// stage combinations.
+// (vjp_wv*.hip), and the adjoints of the field conversions.
 #include "vjp_impl.h"
 
 namespace mfc {
@@ -12,16 +11,15 @@ MFC_EXTERN_VJP(3)
 MFC_EXTERN_VJP(4)
 
 hipError_t launch_rhs_vjp(int nf, int ndim, const Params& pm, const double* q, const double* rbar, double* qbar,
-                          const VjpScratch& sc, bool accumulate, hipStream_t s, PassTimer* tm, const StageEpi* epi) {
-  StageEpi none{0, 0.0, nullptr, nullptr, nullptr};
-  const StageEpi& ep = (epi && sc.all_axes) ? *epi : none;
+                          double* wsum, bool accumulate, hipStream_t s, PassTimer* tm, const StageEpi* epi) {
+  const StageEpi ep = epi ? *epi : StageEpi{0, 0.0, nullptr, nullptr, nullptr};
   if (pm.nu[0] || pm.nu[1] || pm.nu[2])
-    return launch_rhs_vjp_wv<kWvNonUniform>(nf, ndim, pm, q, rbar, qbar, sc, accumulate, s, tm, ep);
+    return launch_rhs_vjp_wv<kWvNonUniform>(nf, ndim, pm, q, rbar, qbar, wsum, accumulate, s, tm, ep);
   switch (pm.weno_variant) {
-    case 1: return launch_rhs_vjp_wv<1>(nf, ndim, pm, q, rbar, qbar, sc, accumulate, s, tm, ep);
-    case 2: return launch_rhs_vjp_wv<2>(nf, ndim, pm, q, rbar, qbar, sc, accumulate, s, tm, ep);
-    case 3: return launch_rhs_vjp_wv<3>(nf, ndim, pm, q, rbar, qbar, sc, accumulate, s, tm, ep);
-    default: return launch_rhs_vjp_wv<0>(nf, ndim, pm, q, rbar, qbar, sc, accumulate, s, tm, ep);
+    case 1: return launch_rhs_vjp_wv<1>(nf, ndim, pm, q, rbar, qbar, wsum, accumulate, s, tm, ep);
+    case 2: return launch_rhs_vjp_wv<2>(nf, ndim, pm, q, rbar, qbar, wsum, accumulate, s, tm, ep);
+    case 3: return launch_rhs_vjp_wv<3>(nf, ndim, pm, q, rbar, qbar, wsum, accumulate, s, tm, ep);
+    default: return launch_rhs_vjp_wv<0>(nf, ndim, pm, q, rbar, qbar, wsum, accumulate, s, tm, ep);
   }
 }
 
@@ -77,50 +75,6 @@ hipError_t launch_convert_vjp(int nf, int ndim, bool to_cons, const Params& pm, 
   MFC_CASE(2, 3)
 #undef MFC_CASE
   return hipErrorInvalidValue;
-}
-
-// ---------------------------------------------------------------------------
-// reverse SSP-RK3 combinations (Shu-Osher form)
-//   qbar2 = 2/3 (qbar3 + dt v3),  qbarn  = 1/3 qbar3          (v3 = L^T(q2) qbar3)
-//   qbar1 = 1/4 (qbar2 + dt v2),  qbarn += 3/4 qbar2          (v2 = L^T(q1) qbar2)
-//   qbarn += qbar1 + dt v1                                    (v1 = L^T(qn) qbar1)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void adj_stage3_kernel(long long n, double dt, const double* __restrict__ a,
-                                                         const double* __restrict__ v, double* __restrict__ b2,
-                                                         double* __restrict__ qnb) {
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-    const double x = a[e];
-    b2[e] = (2.0 / 3.0) * (x + dt * v[e]);
-    qnb[e] = (1.0 / 3.0) * x;
-  }
-}
-__global__ __launch_bounds__(256) void adj_stage2_kernel(long long n, double dt, const double* __restrict__ b2,
-                                                         const double* __restrict__ v, double* __restrict__ b1,
-                                                         double* __restrict__ qnb) {
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-    const double x = b2[e];
-    b1[e] = 0.25 * (x + dt * v[e]);
-    qnb[e] = qnb[e] + 0.75 * x;
-  }
-}
-__global__ __launch_bounds__(256) void adj_stage1_kernel(long long n, double dt, const double* __restrict__ b1,
-                                                         const double* __restrict__ v, double* __restrict__ qnb) {
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x)
-    qnb[e] = qnb[e] + (b1[e] + dt * v[e]);
-}
-
-hipError_t launch_adj_stage(int which, long long n, double dt, const double* x, const double* v, double* out,
-                            double* qnb, hipStream_t s) {
-  long long nb = (n + 255) / 256;
-  if (nb > 65536) nb = 65536;
-  dim3 grid((unsigned)nb), block(256);
-  if (which == 3)
-    hipLaunchKernelGGL(adj_stage3_kernel, grid, block, 0, s, n, dt, x, v, out, qnb);
-  else if (which == 2)
-    hipLaunchKernelGGL(adj_stage2_kernel, grid, block, 0, s, n, dt, x, v, out, qnb);
-  else
-    hipLaunchKernelGGL(adj_stage1_kernel, grid, block, 0, s, n, dt, x, v, qnb);
-  return hipGetLastError();
 }
 
 }  // namespace mfc
