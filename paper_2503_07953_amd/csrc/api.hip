@@ -544,6 +544,9 @@ template <typename Real>
 hipError_t step_t(const mfc_problem& prob, const mfc::Params& pm, const StepScratch& sc, mfc::PassTimer* tm,
                   Real* q, double cfl, double dt_fixed, double t_remaining, double* dt_user, hipStream_t s) {
   const int nf = prob.num_fluids, nd = prob.ndim;
+  if (mfc::step_in_one_block(nd, pm))
+    return mfc::launch_step1d<Real>(nf, pm, q, cfl, dt_fixed, t_remaining, &sc.scal[0], &sc.scal[1], dt_user, sc.flag, s,
+                                    tm);
   hipError_t e;
   mfc::StageArgs st{1, dt_fixed, nullptr, nullptr};
   // 2D / 3D: the first axis pass of stage 1 forms the signal maxima while it

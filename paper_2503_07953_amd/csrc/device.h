@@ -171,6 +171,17 @@ __host__ __device__ __forceinline__ void prim_to_cons(const Params& pm, const do
   }
 }
 
+// SSP-RK3 stage of one entry, Shu-Osher form (Sec. 3.4): the new value from q^n,
+// q_k and dt times the right-hand side, combined in double.  The products that
+// are fused are written out, so that the passes and the one-block step of a short
+// 1D grid round alike.
+__device__ __forceinline__ double rk3_stage(int stage, double qn, double qk, double dt, double r) {
+  const double qs = fma(dt, r, qk);
+  if (stage == 1) return qs;
+  if (stage == 2) return fma(0.75, qn, 0.25 * qs);
+  return fma(1.0 / 3.0, qn, (2.0 / 3.0) * qs);
+}
+
 // Squared mixture sound speed, the mixture read as one stiffened gas with
 // gamma_m = 1 + 1/Gamma, pi_m = Pi/(Gamma + 1): c^2 = ((Gamma+1) p + Pi)/(Gamma rho).
 __host__ __device__ __forceinline__ double sound_speed_sq(double rho, double p, double Gam, double Pi) {

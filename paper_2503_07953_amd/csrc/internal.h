@@ -63,6 +63,14 @@ hipError_t launch_rhs(int nf, int ndim, const Params& pm, const Real* qk, Real* 
                       Real* qout, StageArgs st, bool final_step, int* flag, hipStream_t s,
                       PassTimer* tm = nullptr, const SignalFuse* sig = nullptr);
 
+// Short 1D grids: a whole SSP-RK3 step of q in place in one block, CFL (dt
+// formed on the device, written to smax_out, dt_out and, if not null, dt_user)
+// or with dt_fixed.
+bool step_in_one_block(int ndim, const Params& pm);
+template <typename Real>
+hipError_t launch_step1d(int nf, const Params& pm, Real* q, double cfl, double dt_fixed, double t_remaining,
+                         double* smax_out, double* dt_out, double* dt_user, int* flag, hipStream_t s, PassTimer* tm);
+
 // Length of the partials buffer that SignalFuse needs for a grid (the block
 // count of the first axis pass; 0 in 1D, where the signal is a kernel of its own).
 long long signal_partials(int ndim, const int* n);

@@ -37,6 +37,27 @@ hipError_t launch_rhs(int nf, int ndim, const Params& pm, const Real* qk, Real* 
   }
 }
 
+template <typename Real>
+hipError_t launch_step1d(int nf, const Params& pm, Real* q, double cfl, double dt_fixed, double t_remaining,
+                         double* smax_out, double* dt_out, double* dt_user, int* flag, hipStream_t s, PassTimer* tm) {
+#define MFC_WV(WV)                                                                                                    \
+  return launch_step1d_wv<WV, Real>(nf, pm, q, cfl, dt_fixed, t_remaining, smax_out, dt_out, dt_user, flag, s, tm)
+  if (pm.nu[0]) MFC_WV(kWvNonUniform);
+  switch (pm.weno_variant) {
+    case 1: MFC_WV(1);
+    case 2: MFC_WV(2);
+    case 3: MFC_WV(3);
+    default: MFC_WV(0);
+  }
+#undef MFC_WV
+}
+
+bool step_in_one_block(int ndim, const Params& pm) { return step1d_fits(ndim, pm); }
+
+template hipError_t launch_step1d<double>(int, const Params&, double*, double, double, double, double*, double*,
+                                          double*, int*, hipStream_t, PassTimer*);
+template hipError_t launch_step1d<float>(int, const Params&, float*, double, double, double, double*, double*, double*,
+                                         int*, hipStream_t, PassTimer*);
 template hipError_t launch_rhs<double>(int, int, const Params&, const double*, double*, const double*,
                                        double*, StageArgs, bool, int*, hipStream_t, PassTimer*,
                                        const SignalFuse*);

@@ -37,6 +37,7 @@
 #include "internal.h"
 #include "lanes.h"
 #include "march_impl.h"
+#include "step1d.h"
 
 namespace mfc {
 
@@ -453,7 +454,6 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
     else if constexpr (MODE & MODE_ACC)
       r = ld_acc<kNT>(&acc[e]) + Dv;
     if constexpr (MODE & MODE_STEP) {
-      // SSP-RK3, Shu-Osher form (Sec. 3.4), combined in double
       const double dt = st.dt_ptr ? *st.dt_ptr : st.dt;
       double uk;
       if constexpr (kCentreFromLds) {
@@ -463,8 +463,6 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
       } else {
         uk = double(qk[e]);
       }
-      const double qs = uk + dt * double(r);
-      double out;
       double qnv = 0.0;
       if (st.stage != 1) {
         if constexpr (kPrefetchQn)
@@ -474,13 +472,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
         else
           qnv = double(qn[e]);
       }
-      if (st.stage == 1)
-        out = qs;
-      else if (st.stage == 2)
-        out = 0.75 * qnv + 0.25 * qs;
-      else
-        out = (1.0 / 3.0) * qnv + (2.0 / 3.0) * qs;
-      qout[e] = Real(out);
+      qout[e] = Real(rk3_stage(st.stage, qnv, uk, dt, double(r)));
     } else {
       st_acc<kNT>(r, &acc[e]);
     }
@@ -644,6 +636,40 @@ hipError_t launch_rhs_wv(int nf, int ndim, const Params& pm, const Real* qk, Rea
   return hipErrorInvalidValue;
 }
 
+// A short 1D grid's whole step (step1d_fits).
+template <int WV, typename Real>
+hipError_t launch_step1d_wv(int nf, const Params& pm, Real* q, double cfl, double dt_fixed, double t_remaining,
+                            double* smax_out, double* dt_out, double* dt_user, int* flag, hipStream_t s,
+                            PassTimer* tm) {
+#define MFC_RS(NF, B)                                                                                             \
+  case B: return launch_step1d_t<NF, Real, WV, B>(pm, q, cfl, dt_fixed, t_remaining, smax_out, dt_out, dt_user, flag, \
+                                                  s, tm);
+  if (nf == 1) {
+    switch (option_bits(pm)) {
+      MFC_RS(1, 0)
+      MFC_RS(1, RS_HLL)
+      MFC_RS(1, RS_THORNBER)
+      MFC_RS(1, RS_HLL | RS_THORNBER)
+      MFC_RS(1, RS_APC)
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (option_bits(pm)) {
+    MFC_RS(2, 0)
+    MFC_RS(2, RS_HLL)
+    MFC_RS(2, RS_THORNBER)
+    MFC_RS(2, RS_HLL | RS_THORNBER)
+    MFC_RS(2, RS_APC)
+    MFC_RS(2, RS_KAPILA)
+    MFC_RS(2, RS_KAPILA | RS_HLL)
+    MFC_RS(2, RS_KAPILA | RS_THORNBER)
+    MFC_RS(2, RS_KAPILA | RS_HLL | RS_THORNBER)
+    MFC_RS(2, RS_KAPILA | RS_APC)
+    default: return hipErrorInvalidValue;
+  }
+#undef MFC_RS
+}
+
 // Explicit instantiation (sweep_wv*.hip) and its extern declaration (sweep.hip).
 #define MFC_SWEEP_DECL(KW, WV)                                                                                      \
   KW template hipError_t launch_rhs_wv<WV, double>(int, int, const Params&, const double*, double*, const double*, \
@@ -651,7 +677,11 @@ hipError_t launch_rhs_wv(int nf, int ndim, const Params& pm, const Real* qk, Rea
                                                    const SignalFuse*);                                            \
   KW template hipError_t launch_rhs_wv<WV, float>(int, int, const Params&, const float*, float*, const float*,     \
                                                   float*, StageArgs, bool, int*, hipStream_t, PassTimer*,         \
-                                                  const SignalFuse*);
+                                                  const SignalFuse*);                                             \
+  KW template hipError_t launch_step1d_wv<WV, double>(int, const Params&, double*, double, double, double, double*, \
+                                                      double*, double*, int*, hipStream_t, PassTimer*);           \
+  KW template hipError_t launch_step1d_wv<WV, float>(int, const Params&, float*, double, double, double, double*,   \
+                                                     double*, double*, int*, hipStream_t, PassTimer*);
 #define MFC_INSTANTIATE_SWEEP(WV) MFC_SWEEP_DECL(, WV)
 #define MFC_EXTERN_SWEEP(WV) MFC_SWEEP_DECL(extern, WV)
 
