@@ -549,8 +549,7 @@ hipError_t step_t(const mfc_problem& prob, const mfc::Params& pm, const StepScra
                                     tm);
   hipError_t e;
   mfc::StageArgs st{1, dt_fixed, nullptr, nullptr};
-  // 2D / 3D: the first axis pass of stage 1 forms the signal maxima while it
-  // loads q^n, and dt is formed on the device before the x pass reads it
+  // 2D / 3D: dt is formed on the device inside the first stage (SignalFuse)
   mfc::SignalFuse sig{sc.partial, cfl, t_remaining, &sc.scal[0], &sc.scal[1], dt_user};
   const mfc::SignalFuse* sigp = nullptr;
   if (cfl > 0.0) {

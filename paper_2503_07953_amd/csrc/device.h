@@ -959,22 +959,24 @@ __host__ __device__ __forceinline__ bool hll(const Params& pm, const T* WL, cons
   }
   const T EL = GamL * pL + PiL + T(0.5) * rhoL * usqL;
   const T ER = GamR * pR + PiR + T(0.5) * rhoR * usqR;
+  // (fused as written, so that every kernel rounds alike)
+  auto flux = [&](T fL, T fR, T dU) { return fma(cT, dU, fma(bT, fR, aT * fL)) * rT; };
 #pragma unroll
-  for (int i = 0; i < NF; ++i) F[i] = (aT * (WL[i] * unL) + bT * (WR[i] * unR) + cT * (WR[i] - WL[i])) * rT;
+  for (int i = 0; i < NF; ++i) F[i] = flux(WL[i] * unL, WR[i] * unR, WR[i] - WL[i]);
 #pragma unroll
   for (int e = 0; e < D; ++e) {
     const T mL = rhoL * WL[R::MOM + e], mR = rhoR * WR[R::MOM + e];
     const T fL = mL * unL + ((e == DIR) ? pL : T(0));
     const T fR = mR * unR + ((e == DIR) ? pR : T(0));
-    F[R::MOM + e] = (aT * fL + bT * fR + cT * (mR - mL)) * rT;
+    F[R::MOM + e] = flux(fL, fR, mR - mL);
   }
-  F[R::E] = (aT * ((EL + pL) * unL) + bT * ((ER + pR) * unR) + cT * (ER - EL)) * rT;
-  uf = (aT * unL + bT * unR) * rT;
+  F[R::E] = flux((EL + pL) * unL, (ER + pR) * unR, ER - EL);
+  uf = fma(bT, unR, aT * unL) * rT;
   if constexpr (NF == 2) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const T aL = WL[R::ALPHA + k], aR = WR[R::ALPHA + k];
-      F[R::ALPHA + k] = (aT * (aL * unL) + bT * (aR * unR) + cT * (aR - aL)) * rT;
+      F[R::ALPHA + k] = flux(aL * unL, aR * unR, aR - aL);
     }
   }
   bool finite = __builtin_isfinite(uf);

@@ -20,10 +20,12 @@ struct StageArgs {
   double* sig_partial;    // MODE_SIGNAL: one maximum per block of the pass
 };
 
-// CFL time step formed inside the first RHS evaluation of a step (2D and 3D):
-// the first axis pass writes per-block signal maxima to `partial`, then one
-// block forms smax, dt = cfl/smax (clipped to t_remaining when > 0) and
-// writes them to smax_out, dt_out and (if not null) dt_user.
+// CFL time step formed inside the first RHS evaluation of a step (2D and 3D)
+// from block maxima of the signal speed in `partial`: smax, dt = cfl/smax
+// (clipped to t_remaining when > 0), written to smax_out, dt_out and (if not
+// null) dt_user.  3D: the first axis pass writes the maxima and one block
+// reduces them; 2D: a kernel of kReduceBlocks blocks writes them and every block
+// of the stage reduces them for itself.
 struct SignalFuse {
   double* partial;
   double cfl;
@@ -71,12 +73,18 @@ template <typename Real>
 hipError_t launch_step1d(int nf, const Params& pm, Real* q, double cfl, double dt_fixed, double t_remaining,
                          double* smax_out, double* dt_out, double* dt_user, int* flag, hipStream_t s, PassTimer* tm);
 
-// Length of the partials buffer that SignalFuse needs for a grid (the block
-// count of the first axis pass; 0 in 1D, where the signal is a kernel of its own).
+// Length of the partials buffer that SignalFuse needs for a 3D grid (the block
+// count of the first axis pass; 0 in 1D and 2D, where the signal is a kernel of
+// kReduceBlocks blocks).
 long long signal_partials(int ndim, const int* n);
 
 hipError_t launch_finalize_dt(const double* partial, int nparts, double cfl, double t_remaining, double* smax_out,
                               double* dt_out, double* dt_user, hipStream_t s);
+
+// The kReduceBlocks block maxima of the signal speed.
+template <typename Real>
+hipError_t launch_signal_partials(int nf, int ndim, const Params& pm, const Real* q, double* partial, int* flag,
+                                  hipStream_t s);
 
 template <typename Real>
 hipError_t launch_max_signal(int nf, int ndim, const Params& pm, const Real* q, double* partial,

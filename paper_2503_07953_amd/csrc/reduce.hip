@@ -33,12 +33,17 @@ __global__ __launch_bounds__(kReduceThreads) void max_signal_partial(Params pm, 
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) U[v] = double(q[v * nc + c]);
     cons_to_prim<NF, D>(pm, U, W);
-    // 1/h per axis of this cell (tabulated on a non-uniform grid)
-    const long long nx = pm.n[0], ny = pm.n[1];
-    const int idx[3] = {(int)(c % nx), (int)((c / nx) % ny), (int)(c / (nx * ny))};
+    // 1/h per axis of this cell; a non-uniform grid has it tabulated by the
+    // cell's indices (64-bit divisions that a uniform one leaves out)
     double ih[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) ih[d] = inv_width(pm, d, idx[d]);
+    for (int d = 0; d < D; ++d) ih[d] = pm.inv_dx[d];
+    if (pm.nu[0] || pm.nu[1] || pm.nu[2]) {
+      const long long nx = pm.n[0], ny = pm.n[1];
+      const int idx[3] = {(int)(c % nx), (int)((c / nx) % ny), (int)(c / (nx * ny))};
+#pragma unroll
+      for (int d = 0; d < D; ++d) ih[d] = inv_width(pm, d, idx[d]);
+    }
     bool b;
     const double s = cell_signal<NF, D>(pm, U, W, b, ih);
     bad |= b;
@@ -97,9 +102,8 @@ hipError_t launch_finalize_dt(const double* partial, int nparts, double cfl, dou
 }
 
 template <typename Real>
-hipError_t launch_max_signal(int nf, int ndim, const Params& pm, const Real* q, double* partial,
-                             double* smax_out, double cfl, double t_remaining, double* dt_out,
-                             double* dt_user, int* flag, hipStream_t s) {
+hipError_t launch_signal_partials(int nf, int ndim, const Params& pm, const Real* q, double* partial, int* flag,
+                                  hipStream_t s) {
   dim3 grid(kReduceBlocks), block(kReduceThreads);
 #define MFC_CASE(NF, D)                                                                          \
   if (nf == NF && ndim == D) {                                                                   \
@@ -109,11 +113,18 @@ hipError_t launch_max_signal(int nf, int ndim, const Params& pm, const Real* q, 
     return hipErrorInvalidValue;
   }
 #undef MFC_CASE
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(finalize_dt, dim3(1), block, 0, s, partial, kReduceBlocks, cfl, t_remaining, smax_out,
-                     dt_out, dt_user);
   return hipGetLastError();
+}
+template hipError_t launch_signal_partials<double>(int, int, const Params&, const double*, double*, int*, hipStream_t);
+template hipError_t launch_signal_partials<float>(int, int, const Params&, const float*, double*, int*, hipStream_t);
+
+template <typename Real>
+hipError_t launch_max_signal(int nf, int ndim, const Params& pm, const Real* q, double* partial,
+                             double* smax_out, double cfl, double t_remaining, double* dt_out,
+                             double* dt_user, int* flag, hipStream_t s) {
+  const hipError_t e = launch_signal_partials<Real>(nf, ndim, pm, q, partial, flag, s);
+  if (e != hipSuccess) return e;
+  return launch_finalize_dt(partial, kReduceBlocks, cfl, t_remaining, smax_out, dt_out, dt_user, s);
 }
 
 // Block sums of each row; on a non-uniform grid (NU) every cell is weighted by

@@ -12,12 +12,8 @@ MFC_EXTERN_SWEEP(3)
 MFC_EXTERN_SWEEP(4)
 
 long long signal_partials(int ndim, const int* n) {
-  if (ndim == 2) {
-    const long long a = first_pass_blocks<2, double>(n), b = first_pass_blocks<2, float>(n);
-    return a > b ? a : b;
-  }
   if (ndim == 3) {
-    const long long a = first_pass_blocks<3, double>(n), b = first_pass_blocks<3, float>(n);
+    const long long a = first_pass_blocks<double>(n), b = first_pass_blocks<float>(n);
     return a > b ? a : b;
   }
   return 0;

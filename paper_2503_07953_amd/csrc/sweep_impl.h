@@ -3,7 +3,8 @@
 // sweep_wv*.hip translation unit instantiates one variant (so that the
 // variants compile in parallel); sweep.hip dispatches among them.
 // One fused pass per grid axis of the five-equation RHS (the y and x axes of
-// large 3D grids go in one marching pass instead, march_impl.h).
+// large 3D grids go in one marching pass instead, march_impl.h, and both axes of
+// 2D grids in one pass over tiles, plane_impl.h).
 //
 // A pass over axis DIR does, for a tile of cells, in one kernel:
 //   (a) load the conservative state of the tile plus three ghost/halo cells on
@@ -28,7 +29,7 @@
 // Tile shapes (wave64): along x the centres of a tile are the 64 lanes of a
 // wave, one wave per x-row, 4 rows per block; along y and z, 32 x-lanes by 16
 // centres along the sweep axis (512 threads; in FP64, 16 lanes by 16 centres
-// for y in 3D and 16 lanes by 32 centres for z).  Every access to q is to x-
+// for y and 16 lanes by 32 centres for z).  Every access to q is to x-
 // contiguous runs, so all three passes read HBM coalesced without any
 // transposition of the state.
 #pragma once
@@ -37,6 +38,7 @@
 #include "internal.h"
 #include "lanes.h"
 #include "march_impl.h"
+#include "plane_impl.h"
 #include "step1d.h"
 
 namespace mfc {
@@ -61,12 +63,12 @@ template <int DIR, int D, typename Real>
 struct Tile {
   // TA: reconstruction centres per tile along the sweep axis (outputs TA - 2)
   // TB: independent lines across the sweep axis (x lanes for y and z).  In
-  // FP64 the y pass of a 3D stage runs 16 lanes (256-thread blocks, twice the
+  // FP64 the y pass runs 16 lanes (256-thread blocks, twice the
   // blocks per CU) and the z pass 32 centres x 16 lanes (halo loads 36 per 30
   // outputs instead of 20 per 14); both measured faster in FP64, slower in FP32.
   static constexpr bool kF64 = sizeof(Real) == 8;
   static constexpr int TA = (DIR == 0) ? 64 : ((DIR == 2 && kF64) ? 32 : 16);
-  static constexpr int TB = (DIR == 0) ? ((D == 1) ? 1 : 4) : ((kF64 && (DIR == 2 || D == 3)) ? 16 : 32);
+  static constexpr int TB = (DIR == 0) ? ((D == 1) ? 1 : 4) : (kF64 ? 16 : 32);
   static constexpr int NT = TA * TB;
   static constexpr int OUT = TA - 2;
   static constexpr int SA = TA + 4;  // LDS slots along the sweep axis
@@ -523,18 +525,14 @@ static hipError_t launch_one(const Params& pm, const Real* qk, Real* acc, const 
   return hipGetLastError();
 }
 
-// Blocks of the first axis pass of a 2D / 3D evaluation (y in 2D, z in 3D).
-template <int D, typename Real>
+// Blocks of the first axis pass of a 3D evaluation (z).
+template <typename Real>
 static long long first_pass_blocks(const int* n) {
-  using TL = Tile<D - 1, D, Real>;
-  const long long bx = (n[0] + TL::TB - 1) / TL::TB;
-  if constexpr (D == 2)
-    return bx * ((n[1] + TL::OUT - 1) / TL::OUT) * n[2];
-  else
-    return bx * n[1] * ((n[2] + TL::OUT - 1) / TL::OUT);
+  using TL = Tile<2, 3, Real>;
+  return (long long)((n[0] + TL::TB - 1) / TL::TB) * n[1] * ((n[2] + TL::OUT - 1) / TL::OUT);
 }
 
-// The first axis pass (z in 3D, y in 2D).  sig: it also forms the signal-speed
+// The first axis pass of a 3D evaluation (z).  sig: it also forms the signal-speed
 // block maxima, and dt is formed from them.
 template <int NF, int D, typename Real, int WV, int RS>
 static hipError_t launch_first(const Params& pm, const Real* qk, Real* acc, const Real* qn, Real* qout, StageArgs st,
@@ -545,17 +543,16 @@ static hipError_t launch_first(const Params& pm, const Real* qk, Real* acc, cons
   hipError_t e = launch_one<NF, D, FIRST, Real, MODE_WRITE | MODE_SIGNAL, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
   if (e != hipSuccess) return e;
   if (tm) tm->begin(KIND_SIGNAL, s);
-  e = launch_finalize_dt(sig->partial, (int)first_pass_blocks<D, Real>(pm.n), sig->cfl, sig->t_remaining, sig->smax_out,
+  e = launch_finalize_dt(sig->partial, (int)first_pass_blocks<Real>(pm.n), sig->cfl, sig->t_remaining, sig->smax_out,
                          sig->dt_out, sig->dt_user, s);
   if (tm) tm->end(KIND_SIGNAL, s);
   return e;
 }
 
 // All axes of one RHS evaluation.  final_step: the last pass combines into
-// qout.  sig (2D / 3D): the first pass also forms the signal-speed block
-// maxima and dt is formed before the last pass reads it.  From the highest axis
-// down, each in a pass of its own; the y and x axes of large 3D grids in one
-// marching pass (march_pays).
+// qout.  sig (2D / 3D): dt is formed on the way (SignalFuse).  2D: both axes in
+// one pass.  3D: from the highest axis down, each in a pass of its own; the y and
+// x axes of large grids in one marching pass (march_pays).
 template <int NF, int D, typename Real, int WV, int RS>
 static hipError_t launch_rhs_t(const Params& pm, const Real* qk, Real* acc, const Real* qn, Real* qout,
                                StageArgs st, bool final_step, int* flag, hipStream_t s, PassTimer* tm,
@@ -567,19 +564,19 @@ static hipError_t launch_rhs_t(const Params& pm, const Real* qk, Real* acc, cons
       e = launch_one<NF, D, 0, Real, MODE_STEP, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
     else
       e = launch_one<NF, D, 0, Real, MODE_WRITE, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+  } else if constexpr (D == 2) {
+    e = plane_rhs<NF, Real, WV, RS>(pm, qk, acc, qn, qout, st, final_step, flag, s, tm, sig);
   } else {
     e = launch_first<NF, D, Real, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm, sig);
     if (e != hipSuccess) return e;
-    if constexpr (D == 3) {
-      if constexpr (kMarchVariant<WV>) {
-        if (march_pays<Real>(pm)) {
-          if (final_step) return launch_march<NF, Real, MODE_ACC | MODE_STEP, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
-          return launch_march<NF, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
-        }
+    if constexpr (kMarchVariant<WV>) {
+      if (march_pays<Real>(pm)) {
+        if (final_step) return launch_march<NF, Real, MODE_ACC | MODE_STEP, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+        return launch_march<NF, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
       }
-      e = launch_one<NF, D, 1, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
-      if (e != hipSuccess) return e;
     }
+    e = launch_one<NF, D, 1, Real, MODE_ACC, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
+    if (e != hipSuccess) return e;
     if (final_step)
       e = launch_one<NF, D, 0, Real, MODE_ACC | MODE_STEP, WV, RS>(pm, qk, acc, qn, qout, st, flag, s, tm);
     else
