@@ -199,6 +199,43 @@ bool moment_inverse(int deg, const double* e, double* inv) {
   return true;
 }
 
+// Rows NU_B .. of one table entry from its candidates and ideal weights.
+void fold_entry(double* t, long long st) {
+  auto at = [&](int row) -> double& { return t[row * st]; };
+  double value[2][3][2];  // [right, left face][candidate][per D_r, D_{r+1}], less f_2
+  for (int r = 0; r < 3; ++r) {
+    double m0[2], m1[2], m2[2];
+    for (int j = 0; j < 2; ++j) {
+      m0[j] = at(mfc::NU_MU0 + 2 * r + j);
+      m1[j] = at(mfc::NU_M1 + 2 * r + j);
+      m2[j] = at(mfc::NU_M2 + 2 * r + j);
+      value[0][r][j] = m0[j] + 0.5 * m1[j] + 0.25 * m2[j];
+      value[1][r][j] = m0[j] - 0.5 * m1[j] + 0.25 * m2[j];
+    }
+    at(mfc::NU_B + 3 * r) = m1[0] * m1[0] + 13.0 / 3.0 * (m2[0] * m2[0]);
+    at(mfc::NU_B + 3 * r + 1) = 2.0 * (m1[0] * m1[1] + 13.0 / 3.0 * (m2[0] * m2[1]));
+    at(mfc::NU_B + 3 * r + 2) = m1[1] * m1[1] + 13.0 / 3.0 * (m2[1] * m2[1]);
+  }
+  for (int side = 0; side < 2; ++side) {
+    const double(*q)[2] = value[side];
+    // candidate 0 less candidate 1: q00 D_0 + (q01 - q10) D_1 - q11 D_2; candidate
+    // 2 less candidate 1: -q10 D_1 + (q20 - q11) D_2 + q21 D_3.  Both faces have
+    // the same third difference, a multiple of it each.
+    if (side == 0) {
+      at(mfc::NU_A) = -q[0][0] / q[1][1];
+      at(mfc::NU_A + 1) = (q[1][0] - q[0][1]) / q[1][1];
+      at(mfc::NU_C) = -q[2][1] / q[1][0];
+      at(mfc::NU_C + 1) = (q[1][1] - q[2][0]) / q[1][0];
+    }
+    const int w = side == 0 ? mfc::NU_DR : mfc::NU_DL, k = side == 0 ? mfc::NU_KR : mfc::NU_KL;
+    at(k) = -q[1][1] * at(w);
+    at(k + 1) = -q[1][0] * at(w + 2);
+    const int v = side == 0 ? mfc::NU_QR : mfc::NU_QL;
+    at(v) = q[1][0];
+    at(v + 1) = q[1][1];
+  }
+}
+
 // Table of one axis: kNuCoefs rows of n + 6 entries (positions -3 .. n + 2).
 bool build_axis_table(const mfc::Params& pm, int d, const std::vector<double>& faces, double dx,
                       std::vector<double>& tab) {
@@ -257,6 +294,7 @@ bool build_axis_table(const mfc::Params& pm, int d, const std::vector<double>& f
       const int row = side == 0 ? mfc::NU_DR : mfc::NU_DL;
       for (int r = 0; r < 3; ++r) tab[(row + r) * st + pos + 3] = rhs[r];
     }
+    fold_entry(&tab[pos + 3], st);
   }
   return true;
 }

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
   constexpr bool kF64 = sizeof(Real) == 8;
   constexpr bool kStep = (MODE & MODE_STEP) != 0;
   static_assert((MODE & MODE_ACC) != 0, "the z pass comes first");
-  constexpr bool kNU = WV == kWvNonUniform;
+  static_assert(WV != kWvNonUniform, "uniform grids only");
   // two rows of primitives (j - 4 and j - 3), by the parity of the step that
   // wrote them, with two pad cells on both sides for the x stencil
   constexpr int LW = 68;
@@ -133,22 +133,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
     }
   }
   const WenoK<Real> K = weno_consts(Real(pm.eps));
-  // non-uniform grid: the tables of both axes; lanes that are no x centre read
-  // the nearest entry that is one
-  const long long nst = (long long)ny + 6, nstx = (long long)nx + 6;
-  const Real* cfy = nullptr;
-  const Real* cfx = nullptr;
-  if constexpr (kNU) {
-    const int cx = (xpos < -1 ? -1 : (xpos > nx ? nx : xpos)) + 3;
-    if constexpr (kF64) {
-      cfy = (const Real*)pm.nu[1];
-      cfx = (const Real*)pm.nu[0] + cx;
-    } else {
-      cfy = (const Real*)pm.nuf[1];
-      cfx = (const Real*)pm.nuf[0] + cx;
-    }
-  }
-  const Real ihx = Real(kNU ? (out_lane ? inv_width(pm, 0, xpos) : 0.0) : pm.inv_dx[0]);
+  const Real ihx = Real(pm.inv_dx[0]);
 
   // The y stencil of step j: rows j - 4 and j - 3 in LDS, j - 2 .. j in w;
   // wo is row j - 3 on its way into LDS.
@@ -235,10 +220,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
       for (int v = 0; v < NEQ; ++v) {
         const Real* f = so + v * LW + lane;
         Real wl;
-        if constexpr (kNU)
-          weno5_nu(f[0], f[1], f[2], f[3], f[4], K.eps, cfx, nstx, wl, WR[v]);
-        else
-          weno5<WV>(f[0], f[1], f[2], f[3], f[4], K, wl, WR[v]);
+        weno5<WV>(f[0], f[1], f[2], f[3], f[4], K, wl, WR[v]);
         WL[v] = lane_shift<kFromPrev>(wl);
         // one row at a time: interleaved rows cost more registers than there are
         if constexpr (kF64) __builtin_amdgcn_sched_barrier(0);
@@ -273,10 +255,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) {
       const Real f0 = s4[v * LW + own], f1 = so[v * LW + own];
-      if constexpr (kNU)
-        weno5_nu(f0, f1, w[0][v], w[1][v], w[2][v], K.eps, cfy + (j - 2 + 3), nst, WLn[v], WR[v]);
-      else
-        weno5<WV>(f0, f1, w[0][v], w[1][v], w[2][v], K, WLn[v], WR[v]);
+      weno5<WV>(f0, f1, w[0][v], w[1][v], w[2][v], K, WLn[v], WR[v]);
       if constexpr (kF64) __builtin_amdgcn_sched_barrier(0);
     }
     Real F[NEQ], uf;
@@ -300,7 +279,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
           for (int v = 0; v < NEQ; ++v) uk[v] = load_at(qk + v * nc + ob, o);
         }
       }
-      const Real ih = Real(kNU ? inv_width(pm, 1, j - 3) : pm.inv_dx[1]);
+      const Real ih = Real(pm.inv_dx[1]);
       if constexpr (kF64) ufp = sF[NEQ * 64 + lane];
       const Real div = ih * (uf - ufp);
       double Uc[NEQ];

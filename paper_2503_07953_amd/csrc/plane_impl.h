@@ -128,12 +128,6 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   __syncthreads();
 
   const WenoK<Real> K = weno_consts(Real(pm.eps));
-  auto table = [&](int d, int c) -> const Real* {
-    if constexpr (sizeof(Real) == 8)
-      return (const Real*)pm.nu[d] + (c + 3);
-    else
-      return (const Real*)pm.nuf[d] + (c + 3);
-  };
   const bool out_ok = a >= 1 && a <= TL::OX && k < TL::OY && cx < nx && cy < ny;
   // volume fractions of the centre for the alpha source; with RS_KAPILA they
   // carry Kapila's K of the cell
@@ -158,12 +152,13 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
     Real WLc[NEQ], WL[NEQ], WR[NEQ], F[NEQ], uf = Real(0);
     const bool centre = cy < ny && cx <= nx;
     if (centre) {
-      const Real* cf = kNU ? table(0, cx) : nullptr;
+      NuK<Real> KN;
+      if constexpr (kNU) KN = nu_entry<Real>(pm, 0, cx);
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) {
         const Real* f = sh + v * LS + own;
         if constexpr (kNU)
-          weno5_nu(f[-2], f[-1], f[0], f[1], f[2], K.eps, cf, (long long)nx + 6, WLc[v], WR[v]);
+          weno5_nu(f[-2], f[-1], f[0], f[1], f[2], K.eps, KN, WLc[v], WR[v]);
         else
           weno5<WV>(f[-2], f[-1], f[0], f[1], f[2], K, WLc[v], WR[v]);
       }
@@ -190,13 +185,14 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   const bool centre = a >= 1 && a <= TL::OX && cx < nx && cy <= ny;
   Real WL[NEQ], WR[NEQ], F[NEQ], uf = Real(0);
   if (centre) {
-    const Real* cf = kNU ? table(1, cy) : nullptr;
+    NuK<Real> KN;
+    if constexpr (kNU) KN = nu_entry<Real>(pm, 1, cy);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) {
       const Real* f = sh + v * LS + own;
       constexpr int S = TL::SX;
       if constexpr (kNU)
-        weno5_nu(f[-2 * S], f[-S], f[0], f[S], f[2 * S], K.eps, cf, (long long)ny + 6, WL[v], WR[v]);
+        weno5_nu(f[-2 * S], f[-S], f[0], f[S], f[2 * S], K.eps, KN, WL[v], WR[v]);
       else
         weno5<WV>(f[-2 * S], f[-S], f[0], f[S], f[2 * S], K, WL[v], WR[v]);
     }

@@ -105,18 +105,13 @@ __global__ __launch_bounds__(kStep1dThreads) void step1d_kernel(Params pm, Real*
     Real al[2] = {Real(0), Real(0)};
     if (centre) {
       const WenoK<Real> K = weno_consts(Real(pm.eps));
-      const Real* cf = nullptr;
-      if constexpr (WV == kWvNonUniform) {
-        if constexpr (sizeof(Real) == 8)
-          cf = (const Real*)pm.nu[0] + (c + 3);
-        else
-          cf = (const Real*)pm.nuf[0] + (c + 3);
-      }
+      NuK<Real> KN;
+      if constexpr (WV == kWvNonUniform) KN = nu_entry<Real>(pm, 0, c);
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) {
         const Real* f = sh + v * LS + t;
         if constexpr (WV == kWvNonUniform)
-          weno5_nu(f[0], f[1], f[2], f[3], f[4], K.eps, cf, (long long)n + 6, WLc[v], WR[v]);
+          weno5_nu(f[0], f[1], f[2], f[3], f[4], K.eps, KN, WLc[v], WR[v]);
         else
           weno5<WV>(f[0], f[1], f[2], f[3], f[4], K, WLc[v], WR[v]);
       }

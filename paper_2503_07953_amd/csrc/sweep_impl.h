@@ -149,6 +149,25 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
     org = blockIdx.z * TL::OUT;
   }
 
+  // this thread's reconstruction centre and line
+  const int c = org - 1 + a;
+  int ox = cx, oy = cy, oz = cz;
+  bool line_ok;
+  if constexpr (DIR == 0) {
+    oy += b;
+    line_ok = oy < ny;
+  } else {
+    ox += b;
+    line_ok = ox < nx;
+  }
+  const bool centre_ok = line_ok && c <= nd;
+  // non-uniform grid: the table entry of centre c along this axis, on its way
+  // before the tile's loads
+  NuK<Real> KN;
+  if constexpr (WV == kWvNonUniform) {
+    if (centre_ok) KN = nu_entry<Real>(pm, DIR, c);
+  }
+
   // ---- (a) load + convert the tile and its halo into LDS -------------------
   // MODE_SIGNAL: the signal speed of the tile's own cells (slots 3 .. 2 + OUT,
   // inside the grid) as well; the tiles partition the grid, so the block
@@ -252,18 +271,6 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
     }
   }
 
-  // this thread's reconstruction centre and line
-  const int c = org - 1 + a;
-  int ox = cx, oy = cy, oz = cz;
-  bool line_ok;
-  if constexpr (DIR == 0) {
-    oy += b;
-    line_ok = oy < ny;
-  } else {
-    ox += b;
-    line_ok = ox < nx;
-  }
-  const bool centre_ok = line_ok && c <= nd;
 
   // The accumulator of this thread's output cell is loaded here, so that its
   // latency hides behind the reconstruction: in the y pass, and in the float
@@ -300,15 +307,6 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   Real alpha_cell[2] = {Real(0), Real(0)};
   if (centre_ok) {
     const WenoK<Real> K = weno_consts(Real(pm.eps));
-    // non-uniform grid: the table entry of centre c along this axis
-    const long long nst = (long long)nd + 6;
-    const Real* cf = nullptr;
-    if constexpr (WV == kWvNonUniform) {
-      if constexpr (sizeof(Real) == 8)
-        cf = (const Real*)pm.nu[DIR] + (c + 3);
-      else
-        cf = (const Real*)pm.nuf[DIR] + (c + 3);
-    }
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) {
       const Real f0 = sh[lds_index<DIR, D, Real>(v, a + 0, b)];
@@ -317,7 +315,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
       const Real f3 = sh[lds_index<DIR, D, Real>(v, a + 3, b)];
       const Real f4 = sh[lds_index<DIR, D, Real>(v, a + 4, b)];
       if constexpr (WV == kWvNonUniform)
-        weno5_nu(f0, f1, f2, f3, f4, K.eps, cf, nst, WLc[v], WRc[v]);
+        weno5_nu(f0, f1, f2, f3, f4, K.eps, KN, WLc[v], WRc[v]);
       else
         weno5<WV>(f0, f1, f2, f3, f4, K, WLc[v], WRc[v]);
     }

@@ -207,10 +207,12 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
   const WenoK<double> K = weno_consts(pm.eps);
   const long long nst = (long long)nd + 6;
   const double* cf = nullptr;
+  NuK<double> KN;
   if constexpr (kNU) {
     // table entries of the centres -1 .. n (wrapped positions: their cell's)
     const int ct = wrap ? cell_i : (pos < -1 ? -1 : (pos > nd ? nd : pos));
     cf = pm.nu[DIR] + (ct + 3);
+    KN = nu_entry<double>(pm, DIR, ct);
   }
 
   // ---- (b) WENO at the centre; the left state of the low face from the lane below
@@ -219,7 +221,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
   for (int v = 0; v < NEQ; ++v) {
     double wl;
     if constexpr (kNU)
-      weno5_nu(Wat(v, 0), Wat(v, 1), Wat(v, 2), Wat(v, 3), Wat(v, 4), pm.eps, cf, nst, wl, WR[v]);
+      weno5_nu(Wat(v, 0), Wat(v, 1), Wat(v, 2), Wat(v, 3), Wat(v, 4), pm.eps, KN, wl, WR[v]);
     else
       weno5<WV>(Wat(v, 0), Wat(v, 1), Wat(v, 2), Wat(v, 3), Wat(v, 4), K, wl, WR[v]);
     WL[v] = lane_shift<kFromPrev>(wl);
