@@ -74,6 +74,18 @@ struct Tile {
   static constexpr int SA = TA + 4;  // LDS slots along the sweep axis
 };
 
+// Neighbouring blocks of the 3D x pass that run on one XCD.
+constexpr unsigned kXGroup = 4;
+
+// Start of a launch of the 3D x pass: the line and the place in it that its
+// first wave starts at, its blocks, and the tiles a line (0: the lines run on).
+struct SegBase {
+  long long line;
+  unsigned rem;
+  unsigned blocks;
+  unsigned tiles;
+};
+
 // LDS index of (row v, slot s along the sweep axis, line b).
 template <int DIR, int D, typename Real>
 __device__ __forceinline__ int lds_index(int v, int s, int b) {
@@ -89,7 +101,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
                                                                  Real* __restrict__ acc,
                                                                  const Real* __restrict__ qn,
                                                                  Real* __restrict__ qout, StageArgs st,
-                                                                 int* __restrict__ flag, long long block_base) {
+                                                                 int* __restrict__ flag, SegBase seg) {
   using R = Rows<NF, D>;
   using TL = Tile<DIR, D, Real>;
   constexpr int NEQ = R::NEQ;
@@ -101,6 +113,13 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   // centre's conservative values from them instead of a second read of q_k.
   constexpr bool kLaneX = DIR == 0;
   static_assert(!kLaneX || TL::TA == 64, "an x tile row is one wave");
+  // In 3D a wave's 64 lanes are consecutive positions of all x lines, each with
+  // its three ghosts on both sides, one after the other (lanes 1 .. 62 are
+  // outputs), so that no lane is lost to the grid's size: a line of 64 cells takes
+  // 1.13 waves instead of two tiles, one of 128 takes 2.2 instead of three.
+  // Two-fluid RHS, us, before / now: FP64 64^3 42.3 / 38.6, 20 x 150 x 100 66.1 / 58.8,
+  // 128 x 96 x 80 tabulated 154 / 147; FP32 64^3 37.1 / 34.3, 128^3 175 / 167.
+  constexpr bool kLines = DIR == 0 && D > 1;
   constexpr bool kCentreFromLds = kLaneX && sizeof(Real) == 8 && (MODE & MODE_STEP) != 0;
 
   const int nx = pm.n[0], ny = pm.n[1];
@@ -110,25 +129,45 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
 
   // tile origin (first output cell along DIR) and the fixed coordinates
   int a, b, org, cx = 0, cy = 0, cz = 0;
-  if constexpr (DIR == 0 && D > 1) {
-    // One-dimensional grid.  Blocks are dispatched to the eight XCDs in turn
-    // (block L to XCD L mod 8); XCD k takes the x tiles of row group
-    // 8 g + k in order (g = (L / 8) / tiles per row), so neighbouring x tiles,
-    // which share the 128-byte lines at their edges and their halo, run on
-    // one XCD one after the other, while the eight XCDs work on adjacent
-    // row groups at any time.
+  // x pass of a 3D grid: where the block's first wave starts (its line, and the
+  // place in that line, in positions or in tiles), and from there the line (from
+  // the block's first on) and position of slot s of wave w.
+  const unsigned P = seg.tiles ? seg.tiles : (unsigned)nx + 6u;
+  const float inv_p = 1.0f / float(P);
+  unsigned rem_b = 0;
+  auto place = [&](int w, int s, unsigned& line, int& pos) {
+    // at most 4 x 62 + 6 past a line's end: the quotient is off by one at most
+    const unsigned u = rem_b + (unsigned)(seg.tiles ? w : w * TL::OUT + s);
+    unsigned q = (unsigned)(float(u) * inv_p);
+    int rem = (int)(u - q * P);
+    if (rem < 0) {
+      --q;
+      rem += (int)P;
+    } else if (rem >= (int)P) {
+      ++q;
+      rem -= (int)P;
+    }
+    line = q;
+    pos = (seg.tiles ? rem * TL::OUT + s : rem) - 3;
+  };
+  long long cell_b = 0;     // first cell of the block's first line
+  unsigned lines_left = 0;  // lines from there on, as far as a block gets
+  if constexpr (kLines) {
+    // Blocks are dispatched to the eight XCDs in turn: groups of kXGroup
+    // neighbouring blocks, which share the 128-byte lines at their edges and
+    // their halo, run on one XCD.
     a = threadIdx.x;
     b = threadIdx.y;
-    const long long ntx = (nx + TL::OUT - 1) / TL::OUT;
-    const long long nrg_y = (ny + TL::TB - 1) / TL::TB;
-    const long long L = block_base + blockIdx.x;  // launches come in chunks that start at multiples of 8
-    const long long j = L >> 3;
-    const long long g = j / ntx;
-    const long long rg = g * 8 + (L & 7);
-    if (rg >= nrg_y * pm.n[2]) return;  // padding blocks of the last group of eight
-    org = (int)(j - g * ntx) * TL::OUT;
-    cz = (int)(rg / nrg_y);
-    cy = (int)(rg - cz * nrg_y) * TL::TB;  // + line
+    org = 0;
+    const unsigned j8 = blockIdx.x >> 3;
+    const unsigned block = ((j8 / kXGroup) * 8u + (blockIdx.x & 7u)) * kXGroup + j8 % kXGroup;
+    if (block >= seg.blocks) return;
+    const unsigned r0 = seg.rem + block * (unsigned)(seg.tiles ? TL::TB : TL::OUT * TL::TB);
+    const unsigned q0 = r0 / P;
+    const long long line_b = seg.line + q0, left = (long long)ny * pm.n[2] - line_b;
+    rem_b = r0 - q0 * P;
+    cell_b = line_b * nx;
+    lines_left = left < 256 ? (unsigned)left : 256u;
   } else if constexpr (DIR == 0) {
     a = threadIdx.x;
     b = threadIdx.y;
@@ -150,17 +189,21 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   }
 
   // this thread's reconstruction centre and line
-  const int c = org - 1 + a;
+  int c = org - 1 + a;
   int ox = cx, oy = cy, oz = cz;
+  unsigned own_line = 0;
   bool line_ok;
-  if constexpr (DIR == 0) {
+  if constexpr (kLines) {
+    place(b, a + 2, own_line, c);
+    line_ok = own_line < lines_left;
+  } else if constexpr (DIR == 0) {
     oy += b;
     line_ok = oy < ny;
   } else {
     ox += b;
     line_ok = ox < nx;
   }
-  const bool centre_ok = line_ok && c <= nd;
+  const bool centre_ok = line_ok && c <= nd && (!kLines || c >= -1);
   // non-uniform grid: the table entry of centre c along this axis, on its way
   // before the tile's loads
   NuK<Real> KN;
@@ -190,6 +233,8 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   bool live[kIt], flip[kIt];
   auto load_cell = [&](int it) {
     const int L = tid + it * TL::NT;
+    live[it] = L < kCells;
+    if (kLines && !live[it]) return;
     int s, bb;
     if constexpr (DIR == 0) {
       bb = L / TL::SA;
@@ -198,10 +243,14 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
       s = L / TL::TB;
       bb = L - s * TL::TB;
     }
-    const int pos = org - 3 + s;
+    int pos = org - 3 + s;
     int ix = cx, iy = cy, iz = cz;
     bool inb;
-    if constexpr (DIR == 0) {
+    unsigned ln = 0;
+    if constexpr (kLines) {
+      place(bb, s, ln, pos);
+      inb = ln < lines_left;
+    } else if constexpr (DIR == 0) {
       iy += bb;
       inb = iy < ny;
     } else {
@@ -221,7 +270,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
     cix[it][0] = ix;
     cix[it][1] = iy;
     cix[it][2] = iz;
-    const long long cell = ((long long)iz * ny + iy) * nx + ix;
+    const long long cell = kLines ? cell_b + (ln * (unsigned)nx + (unsigned)ix) : ((long long)iz * ny + iy) * nx + ix;
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) U[it][v] = double(qk[v * nc + cell]);
   };
@@ -287,7 +336,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   Real preq[kPrefetchQn ? NEQ : 1];
   if constexpr (kPrefetch) {
     if (line_ok && a >= 1 && a <= TL::TA - 2 && c >= 0 && c < nd) {
-      const long long cell = (DIR == 1) ? ((long long)oz * ny + c) * nx + ox : ((long long)oz * ny + oy) * nx + c;
+      const long long cell = (DIR == 1) ? ((long long)oz * ny + c) * nx + ox : cell_b + (own_line * (unsigned)nx + (unsigned)c);
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) pre[v] = ld_acc<kNT>(&acc[v * nc + cell]);
       if constexpr (kPrefetchQn) {
@@ -342,7 +391,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   // ---- (c) HLLC at the face c-1/2 between centres c-1 (left) and c (right) ----
   Real F[NEQ];
   Real uf = Real(0);
-  const bool face_ok = centre_ok && a >= 1;
+  const bool face_ok = centre_ok && a >= 1 && (!kLines || c >= 0);
   Real WL[NEQ];
   if constexpr (kLaneX) {
 #pragma unroll
@@ -382,7 +431,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
   if constexpr (DIR == 0) ox = c;
   else if constexpr (DIR == 1) oy = c;
   else oz = c;
-  const long long cell = ((long long)oz * ny + oy) * nx + ox;
+  const long long cell = kLines ? cell_b + (int)(own_line * (unsigned)nx + (unsigned)c) : ((long long)oz * ny + oy) * nx + ox;
   // (x pass: every lane gets here, but only an output lane, 0 <= c < nd, may
   // read the width table)
   const Real inv_dx = Real((WV == kWvNonUniform) ? (out_ok ? inv_width(pm, DIR, c) : 0.0) : pm.inv_dx[DIR]);
@@ -489,19 +538,25 @@ static hipError_t launch_one(const Params& pm, const Real* qk, Real* acc, const 
   dim3 block, grid;
   const int nx = pm.n[0], ny = pm.n[1], nz = pm.n[2];
   if constexpr (DIR == 0 && D > 1) {
-    // x tiles over groups of eight row groups, launched in chunks of at most
-    // 2^24 blocks (64 x 2^24 work-items along x stays below 2^32); every chunk
-    // starts at a multiple of 8 so that block L keeps XCD L mod 8
+    // segments of all x lines, launched in chunks of at most 2^22 blocks
     block = dim3(TL::TA, TL::TB, 1);
-    const long long groups = (long long)((ny + TL::TB - 1) / TL::TB) * nz;
-    const long long total = (long long)((nx + TL::OUT - 1) / TL::OUT) * ((groups + 7) / 8) * 8;
-    constexpr long long kChunk = 1ll << 24;
+    // (whole tiles where they need no more waves, nx up to 6 below a multiple of
+    // 62, and where they fit the chip at once, two waves per SIMD: there the
+    // extra divisions only lengthen a wave, 30^3 18.1 us against 18.7)
+    const long long k = (nx + TL::OUT - 1) / TL::OUT, rows = (long long)ny * nz;
+    const bool tiles = k * TL::OUT <= nx + 6 || k * rows <= 2048;
+    const long long P = tiles ? k : nx + 6;                        // places a line,
+    const long long step = tiles ? TL::TB : TL::OUT * TL::TB;  // places a block
+    const long long blocks = (rows * P - (tiles ? 0 : 6) + step - 1) / step;
+    constexpr long long kChunk = 1ll << 22;
     hipError_t e = hipSuccess;
     if (tm) tm->begin(KIND_PASS_X, s);
-    for (long long base = 0; base < total && e == hipSuccess; base += kChunk) {
-      const long long nb = (total - base < kChunk) ? total - base : kChunk;
-      hipLaunchKernelGGL((sweep_kernel<NF, D, DIR, Real, MODE, WV, RS>), dim3((unsigned)nb, 1, 1), block, 0, s, pm, qk,
-                         acc, qn, qout, st, flag, base);
+    for (long long base = 0; base < blocks && e == hipSuccess; base += kChunk) {
+      const long long nb = (blocks - base < kChunk) ? blocks - base : kChunk;
+      const SegBase seg{base * step / P, (unsigned)(base * step % P), (unsigned)nb, tiles ? (unsigned)k : 0u};
+      const unsigned grid1 = (unsigned)((nb + 8 * kXGroup - 1) / (8 * kXGroup) * (8 * kXGroup));
+      hipLaunchKernelGGL((sweep_kernel<NF, D, DIR, Real, MODE, WV, RS>), dim3(grid1, 1, 1), block, 0, s, pm, qk, acc, qn,
+                         qout, st, flag, seg);
       e = hipGetLastError();
     }
     if (tm) tm->end(KIND_PASS_X, s);
@@ -518,7 +573,7 @@ static hipError_t launch_one(const Params& pm, const Real* qk, Real* acc, const 
   }
   if (tm) tm->begin(KIND_PASS_X + DIR, s);
   hipLaunchKernelGGL((sweep_kernel<NF, D, DIR, Real, MODE, WV, RS>), grid, block, 0, s, pm, qk, acc, qn, qout, st,
-                     flag, 0ll);
+                     flag, SegBase{});
   if (tm) tm->end(KIND_PASS_X + DIR, s);
   return hipGetLastError();
 }
