@@ -36,11 +36,23 @@ struct PlaneTile {
 // signal maxima of `sig`.  Every block reduces them for itself, two loads a
 // thread behind the tile's own, and block 0 writes dt out: a launch less than a
 // reduction of its own (4.4 us).
+// The cells of an axis shared out evenly over its tiles.  (A last tile of two or
+// four columns takes up to twice a full one's time, as in the axis passes: 92 x 53
+// FP64 15.1 us an RHS with full tiles first, 8.7 evenly.)
+struct PlaneAxis {
+  int width, more;  // cells a tile; the first `more` tiles have one more
+  __host__ __device__ int start(int t) const { return t * width + (t < more ? t : more); }
+};
+struct PlaneSplit {
+  unsigned ntx;
+  PlaneAxis x, y;
+};
+
 template <int NF, typename Real, int MODE, int WV, int RS>
 __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const Real* __restrict__ qk,
                                                               Real* __restrict__ acc, const Real* __restrict__ qn,
                                                               Real* __restrict__ qout, StageArgs st, SignalFuse sig,
-                                                              int* __restrict__ flag, unsigned ntx, unsigned base,
+                                                              int* __restrict__ flag, PlaneSplit split, unsigned base,
                                                               unsigned tiles) {
   constexpr int D = 2;
   using R = Rows<NF, D>;
@@ -60,7 +72,9 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   if (tile >= tiles) return;
   const int nx = pm.n[0], ny = pm.n[1];
   const long long nc = pm.ncell;
-  const int ox = (int)(tile % ntx) * TL::OX, oy = (int)(tile / ntx) * TL::OY;
+  const int ix = (int)(tile % split.ntx), iy = (int)(tile / split.ntx);
+  const int ox = split.x.start(ix), oy = split.y.start(iy);
+  const int wx = split.x.start(ix + 1) - ox, wy = split.y.start(iy + 1) - oy;  // this tile's outputs
 
   // this thread's centre: the last wave takes the two rows outside the output
   // rows, which the x axis has no work for
@@ -80,7 +94,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   px[0] = cx;
   py[0] = cy;
   slot[0] = own;
-  live[0] = cx <= nx + 2 && cy <= ny + 2;
+  live[0] = a <= wx + 3 && r <= wy + 3;
   {
     int sx, sy;
     if (tid < kHaloX) {
@@ -95,7 +109,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
     px[1] = ox - 3 + sx;
     py[1] = oy - 3 + sy;
     slot[1] = sy * TL::SX + sx;
-    live[1] = tid < kHaloX + kHaloY && px[1] <= nx + 2 && py[1] <= ny + 2;
+    live[1] = tid < kHaloX + kHaloY && sx <= wx + 5 && sy <= wy + 5;
   }
   Real raw[2][NEQ];
   bool fx[2], fy[2];
@@ -128,7 +142,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   __syncthreads();
 
   const WenoK<Real> K = weno_consts(Real(pm.eps));
-  const bool out_ok = a >= 1 && a <= TL::OX && k < TL::OY && cx < nx && cy < ny;
+  const bool out_ok = a >= 1 && a <= wx && r >= 1 && r <= wy;
   // volume fractions of the centre for the alpha source; with RS_KAPILA they
   // carry Kapila's K of the cell
   Real al[2] = {Real(0), Real(0)};
@@ -150,7 +164,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   Real dx[NEQ];
   if (k < TL::OY) {
     Real WLc[NEQ], WL[NEQ], WR[NEQ], F[NEQ], uf = Real(0);
-    const bool centre = cy < ny && cx <= nx;
+    const bool centre = r <= wy && a <= wx + 1;
     if (centre) {
       NuK<Real> KN;
       if constexpr (kNU) KN = nu_entry<Real>(pm, 0, cx);
@@ -182,7 +196,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
   }
 
   // ---- y axis -----------------------------------------------------------------
-  const bool centre = a >= 1 && a <= TL::OX && cx < nx && cy <= ny;
+  const bool centre = a >= 1 && a <= wx && r <= wy + 1;
   Real WL[NEQ], WR[NEQ], F[NEQ], uf = Real(0);
   if (centre) {
     NuK<Real> KN;
@@ -275,8 +289,9 @@ template <int NF, typename Real, int MODE, int WV, int RS>
 static hipError_t launch_plane(const Params& pm, const Real* qk, Real* acc, const Real* qn, Real* qout, StageArgs st,
                                int* flag, hipStream_t s, PassTimer* tm, const SignalFuse* sig) {
   using TL = PlaneTile;
-  const unsigned ntx = (unsigned)((pm.n[0] + TL::OX - 1) / TL::OX);
-  const unsigned tiles = ntx * (unsigned)((pm.n[1] + TL::OY - 1) / TL::OY);
+  const int ntx = (pm.n[0] + TL::OX - 1) / TL::OX, nty = (pm.n[1] + TL::OY - 1) / TL::OY;
+  const unsigned tiles = (unsigned)ntx * (unsigned)nty;
+  const PlaneSplit split{(unsigned)ntx, {pm.n[0] / ntx, pm.n[0] % ntx}, {pm.n[1] / nty, pm.n[1] % nty}};
   if (tm) tm->begin(KIND_PASS_X, s);
   // chunks of 2^22 blocks keep the work-items of a launch below 2^32
   constexpr unsigned kChunk = 1u << 22;
@@ -284,7 +299,7 @@ static hipError_t launch_plane(const Params& pm, const Real* qk, Real* acc, cons
   for (unsigned base = 0; base < tiles && e == hipSuccess; base += kChunk) {
     const unsigned end = (tiles - base < kChunk) ? tiles : base + kChunk;
     hipLaunchKernelGGL((plane_kernel<NF, Real, MODE, WV, RS>), dim3((end - base + 7) / 8 * 8), dim3(TL::NT), 0, s, pm, qk,
-                       acc, qn, qout, st, sig ? *sig : SignalFuse{}, flag, ntx, base, end);
+                       acc, qn, qout, st, sig ? *sig : SignalFuse{}, flag, split, base, end);
     e = hipGetLastError();
   }
   if (tm) tm->end(KIND_PASS_X, s);
