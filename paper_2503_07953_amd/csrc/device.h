@@ -126,8 +126,12 @@ __host__ __device__ __forceinline__ double fast_rcp(double x) {
 
 // Conservative -> primitive for one cell, in double (the pressure inversion
 // from total energy stays in double in both precision forms):
-// u = (rho u)/rho, p = (rho E - rho |u|^2/2 - Pi)/Gamma.
-template <int NF, int D>
+// u = (rho u)/rho, p = (rho E - rho |u|^2/2 - Pi)/Gamma.  The double form takes Pi
+// off first: in a liquid Pi makes up nearly all of rho E, so that difference is
+// exact and p does not carry a rounding at the size of rho E; prim_to_cons adds Pi
+// last, which gives back the rho E that p came from.  (Rounding at that size is
+// what drives the momentum's error.)  The float form keeps its order.
+template <int NF, int D, typename Real>
 __host__ __device__ __forceinline__ void cons_to_prim(const Params& pm, const double* U, double* W) {
   using R = Rows<NF, D>;
   double rho = U[0];
@@ -145,7 +149,10 @@ __host__ __device__ __forceinline__ void cons_to_prim(const Params& pm, const do
     mixture<NF, double>(pm, U[R::ALPHA], U[R::ALPHA + 1], Gam, Pi);
   else
     mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
-  W[R::E] = (U[R::E] - 0.5 * rho * usq - Pi) * fast_rcp(Gam);
+  if constexpr (sizeof(Real) == 8)
+    W[R::E] = ((U[R::E] - Pi) - 0.5 * rho * usq) * fast_rcp(Gam);
+  else
+    W[R::E] = (U[R::E] - 0.5 * rho * usq - Pi) * fast_rcp(Gam);
 #pragma unroll
   for (int i = 0; i < NF; ++i) W[i] = U[i];
   if constexpr (NF == 2) {
@@ -156,7 +163,7 @@ __host__ __device__ __forceinline__ void cons_to_prim(const Params& pm, const do
 
 // Primitive -> conservative for one cell, in double: rho u = rho * u,
 // rho E = Gamma p + Pi + rho |u|^2/2.
-template <int NF, int D>
+template <int NF, int D, typename Real>
 __host__ __device__ __forceinline__ void prim_to_cons(const Params& pm, const double* W, double* U) {
   using R = Rows<NF, D>;
   double rho = W[0];
@@ -172,7 +179,10 @@ __host__ __device__ __forceinline__ void prim_to_cons(const Params& pm, const do
     mixture<NF, double>(pm, W[R::ALPHA], W[R::ALPHA + 1], Gam, Pi);
   else
     mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
-  U[R::E] = Gam * W[R::E] + Pi + 0.5 * rho * usq;
+  if constexpr (sizeof(Real) == 8)
+    U[R::E] = Pi + (Gam * W[R::E] + 0.5 * rho * usq);
+  else
+    U[R::E] = Gam * W[R::E] + Pi + 0.5 * rho * usq;
 #pragma unroll
   for (int i = 0; i < NF; ++i) U[i] = W[i];
   if constexpr (NF == 2) {

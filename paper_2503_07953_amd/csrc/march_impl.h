@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
     for (int v = 0; v < NEQ; ++v) U[v] = double(r[v]);
     U[R::MOM] *= sgnx;
     U[R::MOM + 1] *= flip ? -1.0 : 1.0;
-    cons_to_prim<NF, D>(pm, U, W);
+    cons_to_prim<NF, D, Real>(pm, U, W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) dst[v] = Real(W[v]);
   };
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
         double Wc[NEQ];
 #pragma unroll
         for (int v = 0; v < NEQ; ++v) Wc[v] = double(so[v * LW + own]);
-        prim_to_cons<NF, D>(pm, Wc, Uc);
+        prim_to_cons<NF, D, Real>(pm, Wc, Uc);
       }
       const unsigned o = here(off);
 #pragma unroll

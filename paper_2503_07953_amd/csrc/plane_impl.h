@@ -135,7 +135,7 @@ __global__ __launch_bounds__(PlaneTile::NT) void plane_kernel(Params pm, const R
     for (int v = 0; v < NEQ; ++v) U[v] = double(raw[it][v]);
     if (fx[it]) U[R::MOM] = -U[R::MOM];
     if (fy[it]) U[R::MOM + 1] = -U[R::MOM + 1];
-    cons_to_prim<NF, D>(pm, U, W);
+    cons_to_prim<NF, D, Real>(pm, U, W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) sh[v * LS + slot[it]] = Real(W[v]);
   }

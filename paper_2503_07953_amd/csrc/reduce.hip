@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kReduceThreads) void max_signal_partial(Params pm, 
     double U[NEQ], W[NEQ];
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) U[v] = double(q[v * nc + c]);
-    cons_to_prim<NF, D>(pm, U, W);
+    cons_to_prim<NF, D, Real>(pm, U, W);
     // 1/h per axis of this cell; a non-uniform grid has it tabulated by the
     // cell's indices (64-bit divisions that a uniform one leaves out)
     double ih[D];
@@ -199,9 +199,9 @@ __global__ __launch_bounds__(256) void convert_kernel(Params pm, const Real* __r
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) X[v] = double(in[v * nc + c]);
     if constexpr (TO_CONS) {
-      prim_to_cons<NF, D>(pm, X, Y);
+      prim_to_cons<NF, D, Real>(pm, X, Y);
     } else {
-      cons_to_prim<NF, D>(pm, X, Y);
+      cons_to_prim<NF, D, Real>(pm, X, Y);
     }
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) out[v * nc + c] = Real(Y[v]);

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kStep1dThreads) void step1d_kernel(Params pm, Real*
       double U[NEQ];
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) U[v] = double(qk[v]);
-      cons_to_prim<NF, D>(pm, U, W);
+      cons_to_prim<NF, D, Real>(pm, U, W);
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) sh[v * LS + t + 2] = Real(W[v]);
       if (stage == 1 && cfl > 0.0) {
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kStep1dThreads) void step1d_kernel(Params pm, Real*
       const Real ih = Real(ihd);
       const Real div = ih * (sh[NEQ * LS + t + 1] - uf);
       double Uc[NEQ];
-      if constexpr (sizeof(Real) == 8) prim_to_cons<NF, D>(pm, W, Uc);
+      if constexpr (sizeof(Real) == 8) prim_to_cons<NF, D, Real>(pm, W, Uc);
 #pragma unroll
       for (int v = 0; v < NEQ; ++v) {
         Real r = ih * (F[v] - sh[v * LS + t + 1]);

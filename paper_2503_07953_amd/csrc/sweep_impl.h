@@ -279,7 +279,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
     const int s = slot[it], bb = line[it];
     double W[NEQ];
     if (flip[it]) U[it][R::MOM + DIR] = -U[it][R::MOM + DIR];
-    cons_to_prim<NF, D>(pm, U[it], W);
+    cons_to_prim<NF, D, Real>(pm, U[it], W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) sh[lds_index<DIR, D, Real>(v, s, bb)] = Real(W[v]);
     if constexpr (kSignal) {
@@ -446,7 +446,7 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
       double Wc[NEQ], Uc[NEQ];
 #pragma unroll
       for (int r = 0; r < NEQ; ++r) Wc[r] = w(r);
-      prim_to_cons<NF, D>(pm, Wc, Uc);
+      prim_to_cons<NF, D, Real>(pm, Wc, Uc);
       return Uc[R::E];
     }
     if (v >= R::MOM && v < R::MOM + D) return ((NF == 2) ? w(0) + w(1) : w(0)) * w(v);

@@ -183,7 +183,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
       }
     }
     if (flip) U[R::MOM + DIR] = -U[R::MOM + DIR];
-    cons_to_prim<NF, D>(pm, U, W);
+    cons_to_prim<NF, D, double>(pm, U, W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) sw[(v * TB + bb) * LS + s] = W[v];
   }
