@@ -38,7 +38,9 @@ def pass_bytes_per_cell(kind, neq, esize, ndim, stage_mix=(1, 1, 1)):
     writes the RHS accumulator (read q, write acc), a middle one reads and
     writes it, and the x pass, last, reads q_k, acc and (stages 2 and 3) q^n
     and writes the next stage state.  In 1D the x pass is alone: q_k, q^n,
-    next state.  The signal reduction reads q once.
+    next state.  The signal reduction reads q once.  Large 3D grids take y and
+    x in one launch, counted as pass_x: it moves the x pass's bytes.  2D grids
+    take both axes in one pass_x launch that has no accumulator to read.
     """
     first = {1: "pass_x", 2: "pass_y", 3: "pass_z"}[ndim]
     reads_qn = (0 + 1 + 1) / 3.0
@@ -401,7 +403,9 @@ def main():
     # and the attainable fraction: the larger of the two floors over the time
     roofline = roofline_of(kinds, neq, 8, case.ndim, ncell, "fp64")
     dom, avg_ms = roofline["kernel"], roofline["avg_launch_ms"]
-    flops_cell = FLOPS_PASS_3D2F + (FLOPS_STAGE_UPDATE if dom == "pass_x" else 0)
+    # a pass_x launch without pass_y launches beside it covers both axes
+    axes = 2 if dom == "pass_x" and case.ndim == 3 and not kinds["pass_y"][1] else 1
+    flops_cell = FLOPS_PASS_3D2F * axes + (FLOPS_STAGE_UPDATE if dom == "pass_x" else 0)
     tflops = flops_cell * ncell / (avg_ms * 1e-3) / 1e12
     roofline["fp64_tflops_alg"] = round(tflops, 3)
     roofline["fp64_frac_alg"] = round(flops_cell * ncell / (avg_ms * 1e-3) / FP64_LANE_INSTR_PER_S, 4)

@@ -287,7 +287,9 @@ int mfc_check(mfc_ctx* ctx, void* hip_stream);
  * mfc_step, mfc_rhs and the VJP entry points is bracketed by a pair of HIP
  * events recorded on its own launch stream.  mfc_get_timing waits for the
  * recorded events and returns, per launch kind
- *   0 signal-speed reduction, 1 x pass, 2 y pass, 3 z pass, 4 adjoint passes,
+ *   0 signal-speed reduction, 1 x pass (also the pass that takes x and y
+ *   together: every 2D grid, large 3D grids; and the one-block step of a short
+ *   1D grid), 2 y pass, 3 z pass, 4 adjoint passes,
  * the summed milliseconds (ms_sum[5]) and launch counts (counts[5]) since the
  * previous call, then starts a new interval.  Timing adds two event records
  * per launch; it is off after mfc_create. */

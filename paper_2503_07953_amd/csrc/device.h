@@ -150,7 +150,7 @@ __host__ __device__ __forceinline__ void cons_to_prim(const Params& pm, const do
   else
     mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
   if constexpr (sizeof(Real) == 8)
-    W[R::E] = ((U[R::E] - Pi) - 0.5 * rho * usq) * fast_rcp(Gam);
+    W[R::E] = fma(-0.5 * rho, usq, U[R::E] - Pi) * fast_rcp(Gam);
   else
     W[R::E] = (U[R::E] - 0.5 * rho * usq - Pi) * fast_rcp(Gam);
 #pragma unroll
@@ -180,7 +180,7 @@ __host__ __device__ __forceinline__ void prim_to_cons(const Params& pm, const do
   else
     mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
   if constexpr (sizeof(Real) == 8)
-    U[R::E] = Pi + (Gam * W[R::E] + 0.5 * rho * usq);
+    U[R::E] = Pi + fma(0.5 * rho, usq, Gam * W[R::E]);
   else
     U[R::E] = Gam * W[R::E] + Pi + 0.5 * rho * usq;
 #pragma unroll

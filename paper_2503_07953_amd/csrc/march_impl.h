@@ -12,7 +12,7 @@
 // What it replaces: a y pass and an x pass that each read q and converted it,
 // and handed the RHS accumulator from one to the other through memory.  At
 // 256^3 in FP64 (two fluids) the two passes moved 428 B per cell and took 668 +
-// 775 us, at the rate of a large copy; this one moves 235 B and takes 1078 us.
+// 775 us, at the rate of a large copy; this one moves 268 B and takes 1068 us.
 // The FP32 form is bound by its instructions (94 % of the issue rate at two
 // waves per SIMD): 409 + 529 us before, 892 us now.  Rounding is that of the
 // separate passes (FP32: bit for bit).
@@ -382,8 +382,9 @@ constexpr bool kMarchVariant = WV <= 1;
 // marching, us per two-fluid step: FP64 64^3 129 / 141, 96^3 313 / 308, 150 x 98
 // x 61 452 / 362, 14 x 250 x 250 498 / 422, 128^3 788 / 709, 256^3 5887 / 4801:
 // from 2^19 cells on.  FP32, which the instructions bound: 128^3 561 / 569,
-// 160^3 1007 / 1079, 256^3 4058 / 3905, 512^3 32399 / 29745: from 2^23 on.  (2D
-// grids gain nothing at any size: 1200^2 290 / 293 and 228 / 274.)
+// 160^3 1007 / 1079, 256^3 4058 / 3905, 512^3 32399 / 29745: from 2^23 on.  Since
+// the x pass runs from line to line: FP64 200^3 2913 / 2400, 256^3 5872 / 4772,
+// FP32 256^3 4065 / 3926.
 template <typename Real>
 inline bool march_pays(const Params& pm) {
   const int* n = pm.n;
