@@ -142,6 +142,7 @@ __host__ __device__ __forceinline__ void weno_js_centre_vjp(double a, double b, 
   const double D0 = b - a, D3 = e - d;
   const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
   const double D1 = w.D1, D2 = w.D2;
+  const double A = (D0 + D2) - 2.0 * D1, B = (D1 + D3) - 2.0 * D2;
   const double m0 = w.s1 * w.s2, m1 = w.s0 * w.s2, m2 = w.s0 * w.s1;
   const double a0 = m0 * m0, a1 = m1 * m1, a2 = m2 * m2;
   const double dl = K.p3 * a2 + (K.p6 * a1 + a0), dr = K.p3 * a0 + (K.p6 * a1 + a2);
@@ -150,20 +151,20 @@ __host__ __device__ __forceinline__ void weno_js_centre_vjp(double a, double b, 
   const double rP = fast_rcp(w.s0 * m0);
   const double l0 = a0 * il, l1 = a1 * il, l2 = a2 * il;
   const double r0 = a0 * ir, r1 = a1 * ir, r2 = a2 * ir;
-  const double A15 = K.p15 * w.A, B15 = K.p15 * w.B;
-  const double tl = l0 * w.A + l2 * B15, tr = r2 * w.B + r0 * A15;
+  const double A15 = 1.5 * A, B15 = 1.5 * B;
+  const double tl = l0 * A + l2 * B15, tr = r2 * B + r0 * A15;
   // cotangents: t_L = -gL/3, t_R = gR/3, h_L = gL/3, h_R = -gR/3
-  const double gl = K.third * gL, gr = K.third * gR;
+  const double gl = (1.0 / 3.0) * gL, gr = (1.0 / 3.0) * gR;
   const double L0 = gl * l0, L2 = gl * l2, R0 = gr * r0, R2 = gr * r2;
   const double tl3 = K.p3 * tl, tr3 = K.p3 * tr;
-  const double g0 = 2.0 * (L0 * (w.A - tl) - R0 * (A15 - tr3)) * (m0 * rP);
+  const double g0 = 2.0 * (L0 * (A - tl) - R0 * (A15 - tr3)) * (m0 * rP);
   const double g1 = 12.0 * (gr * (r1 * tr) - gl * (l1 * tl)) * (m1 * rP);
-  const double g2 = 2.0 * (L2 * (B15 - tl3) - R2 * (w.B - tr)) * (m2 * rP);
-  const double gA = K.p15 * R0 - L0, gB = R2 - K.p15 * L2;
-  gD[0] = gA + g0 * (2.0 * D0 + K.m275 * D1);
-  gD[1] = (gB - 2.0 * gA) + (0.5 * gl - gr) + (g0 * (5.0 * D1 + K.m275 * D0) + g1 * (2.0 * D1 + K.m125 * D2));
-  gD[2] = (gA - 2.0 * gB) + (gl - 0.5 * gr) + (g2 * (5.0 * D2 + K.m275 * D3) + g1 * (2.0 * D2 + K.m125 * D1));
-  gD[3] = gB + g2 * (2.0 * D3 + K.m275 * D2);
+  const double g2 = 2.0 * (L2 * (B15 - tl3) - R2 * (B - tr)) * (m2 * rP);
+  const double gA = 1.5 * R0 - L0, gB = R2 - 1.5 * L2;
+  gD[0] = gA + g0 * (2.0 * D0 + (-2.75) * D1);
+  gD[1] = (gB - 2.0 * gA) + (0.5 * gl - gr) + (g0 * (5.0 * D1 + (-2.75) * D0) + g1 * (2.0 * D1 + (-1.25) * D2));
+  gD[2] = (gA - 2.0 * gB) + (gl - 0.5 * gr) + (g2 * (5.0 * D2 + (-2.75) * D3) + g1 * (2.0 * D2 + (-1.25) * D1));
+  gD[3] = gB + g2 * (2.0 * D3 + (-2.75) * D2);
 }
 
 // Adjoint of the left-biased WENO5-Z value (Sec. 4.2.2) in the same difference

@@ -258,24 +258,27 @@ __host__ __device__ __forceinline__ float sq(float x) { return x * x; }
 
 // Common part of the uniform-grid variants.  With D_0..D_3 the consecutive
 // differences of the five values:
-//   s_k = 3/4 (eps + beta_k): 16/3 of each indicator's difference form
-//     13/3 u^2 + v^2 expands to a binary quadratic form of its two differences
-//     with smallest eigenvalue well above zero (D_0^2 - 11/4 D_0 D_1 + 5/2 D_1^2
-//     and D_1^2 - 5/4 D_1 D_2 + D_2^2), 11 operations for all three instead of
-//     15; the common factor leaves every normalized weight unchanged;
-//   A, B: the two third differences.  The candidates differ from the middle
-//     one by multiples of them, so with weights a_k (of a_0 + 6 a_1 + 3 a_2 on
-//     the left and the mirror image on the right)
-//       f_L = c + (D_2 + D_1/2 - (a_0 A + 3/2 a_2 B)/n_L)/3,
-//       f_R = c - (D_1 + D_2/2 - (a_2 B + 3/2 a_0 A)/n_R)/3:
-//     no candidate is formed, and c is added last, in one rounding.
-// Against sums of weighted candidates this takes a centre and row of WENO5-JS
-// from 58 to 45 double operations; its error against long double is the same
-// on smooth, discontinuous and random data (rms 0.9 to 1.06 times).  Double
-// only: the FP32 form keeps the rounding of its weighted sums.  With the face
-// solver below, the FP64 z pass issues 640 instructions instead of 832 and a
-// 256^3 two-fluid stage takes 1.98 ms instead of 2.14, a 64^3 RHS 38.9 us
-// instead of 44.7.
+//   s_k = 3/4 (eps + beta_k): each indicator's difference form 13/3 u^2 + v^2 is,
+//     but for a factor 16/3, a quadratic form of its two differences, written as a
+//     sum of squares with exact coefficients: (D_0 - 11/8 D_1)^2 + 39/64 D_1^2,
+//     (D_1 - 5/8 D_2)^2 + 39/64 D_2^2, (D_3 - 11/8 D_2)^2 + 39/64 D_2^2; 10
+//     operations for all three instead of 15, nothing cancels, and the common
+//     factor leaves every normalized weight unchanged;
+//   l_k: the candidates' corrections to the centre value, scaled so that each is
+//     one operation: with weights a_k (of a_0 + 6 a_1 + 3 a_2 on the left and the
+//     mirror image on the right)
+//       f_L = c + (a_0 l_0 + 6 a_1 l_1 + 6 a_2 l_2)/(3 n_L),
+//       l_0 = 5/2 D_1 - D_0, l_1 = D_2 + D_1/2, l_2 = D_2 - D_3/4.
+// The corrections are weighted one by one: on the smooth side of a jump the
+// stencils across it have weights of 1e-12 and less, and the value keeps its full
+// accuracy on its own scale (a trace density of 1e-3 beside 1000: 1e-16).  A form
+// that takes the candidates' differences out first is 4 operations shorter (two-
+// fluid FP64 64^3 RHS 35.1 us against 35.7, 200^3 step 2433 against 2486) and
+// leaves 1e-10 there, the rounding of the jump.  A centre and row of WENO5-JS
+// takes 49 double operations, 58 with u, v indicators and six times the
+// corrections; the error against long double is that form's on smooth,
+// discontinuous and random data, local or of the largest value (rms 0.97 to 1.04
+// times).  Double only: the FP32 form keeps the rounding of its weighted sums.
 //
 // The constants come in a struct that a kernel fills once.  In double on the
 // device they are made opaque scalar registers: a known 64-bit constant is
@@ -283,7 +286,7 @@ __host__ __device__ __forceinline__ float sq(float x) { return x * x; }
 // copy wherever the addend is used again (81 copies in the FP64 z pass).
 template <typename T>
 struct WenoK {
-  T eps, e3, m275, p25, m125, p6, p3, p15, third;
+  T eps, e3, m1375, m0625, p0609375, p25, m025, p6, p3;
 };
 __host__ __device__ __forceinline__ double scalar_const(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -297,43 +300,56 @@ __host__ __device__ __forceinline__ WenoK<T> weno_consts(T eps) {
   WenoK<T> k;
   k.eps = eps;
   k.e3 = T(0.75) * eps;
-  k.m275 = scalar_const(T(-2.75));
+  k.m1375 = scalar_const(T(-1.375));
+  k.m0625 = scalar_const(T(-0.625));
+  k.p0609375 = scalar_const(T(0.609375));
   k.p25 = scalar_const(T(2.5));
-  k.m125 = scalar_const(T(-1.25));
+  k.m025 = scalar_const(T(-0.25));
   k.p6 = scalar_const(T(6));
   k.p3 = scalar_const(T(3));
-  k.p15 = scalar_const(T(1.5));
-  k.third = scalar_const(T(1.0 / 3.0));
   return k;
 }
 
 template <typename T>
 struct WenoParts {
-  T D1, D2, A, B, s0, s1, s2;
+  T D0, D1, D2, D3, u0, u1, u2, s0, s1, s2;
 };
 template <typename T>
 __host__ __device__ __forceinline__ WenoParts<T> weno_parts(T a, T b, T c, T d, T e, const WenoK<T>& K) {
   WenoParts<T> w;
   const T D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
-  const T P1 = D1 * D1, P2 = D2 * D2;
-  w.s0 = D0 * (K.m275 * D1 + D0) + (K.p25 * P1 + K.e3);
-  w.s1 = D1 * (K.m125 * D2 + D1) + (P2 + K.e3);
-  w.s2 = D3 * (K.m275 * D2 + D3) + (K.p25 * P2 + K.e3);
-  w.A = (D0 + D2) - T(2) * D1;
-  w.B = (D1 + D3) - T(2) * D2;
+  const T P1 = K.p0609375 * (D1 * D1) + K.e3, P2 = K.p0609375 * (D2 * D2) + K.e3;
+  w.u0 = K.m1375 * D1 + D0;
+  w.u1 = K.m0625 * D2 + D1;
+  w.u2 = K.m1375 * D2 + D3;
+  w.s0 = w.u0 * w.u0 + P1;
+  w.s1 = w.u1 * w.u1 + P2;
+  w.s2 = w.u2 * w.u2 + P2;
+  w.D0 = D0;
   w.D1 = D1;
   w.D2 = D2;
+  w.D3 = D3;
   return w;
 }
 
-// Both biased values from the weighted third differences (nl over the left
-// normalization, nr over the right) with inverse normalizations il, ir.
+// Both biased values from the weights x_k of l_k and y_k of their mirror images
+// (y_0: stencil 2), with il, ir a third of the inverse normalizations.
 template <typename T>
-__host__ __device__ __forceinline__ void weno_values(T c, const WenoParts<T>& w, const WenoK<T>& K, T nl, T il, T nr, T ir,
-                                                    T& fl, T& fr) {
-  const T hl = w.D2 + T(0.5) * w.D1, hr = w.D1 + T(0.5) * w.D2;
-  fl = c + K.third * (hl - nl * il);
-  fr = c - K.third * (hr - nr * ir);
+__host__ __device__ __forceinline__ void weno_values(T c, const WenoParts<T>& w, const WenoK<T>& K, T x0, T x1, T x2, T il,
+                                                    T y0, T y1, T y2, T ir, T& fl, T& fr) {
+  const T l0 = K.p25 * w.D1 - w.D0, l1 = w.D2 + T(0.5) * w.D1, l2 = w.D2 + K.m025 * w.D3;
+  const T r0 = K.p25 * w.D2 - w.D3, r1 = w.D1 + T(0.5) * w.D2, r2 = w.D1 + K.m025 * w.D0;
+  fl = c + (x2 * l2 + (x1 * l1 + x0 * l0)) * il;
+  fr = c - (y2 * r2 + (y1 * r1 + y0 * r0)) * ir;
+}
+// From weights a_0, a_1, a_2 that both sides share up to their ideal ones.
+template <typename T>
+__host__ __device__ __forceinline__ void weno_shared(T c, const WenoParts<T>& w, const WenoK<T>& K, T a0, T a1, T a2, T& fl,
+                                                    T& fr) {
+  const T b0 = K.p6 * a0, b1 = K.p6 * a1, b2 = K.p6 * a2;
+  const T dl = K.p3 * a2 + (b1 + a0), dr = K.p3 * a0 + (b1 + a2);
+  const T inv = fast_rcp(K.p3 * (dl * dr));
+  weno_values(c, w, K, a0, b1, b2, dr * inv, a2, b1, b0, dl * inv, fl, fr);
 }
 
 // FP64 WENO5-JS: the weights d_k/s_k^2 over the common denominator, a_k = the
@@ -342,15 +358,13 @@ __host__ __device__ __forceinline__ void weno_values(T c, const WenoParts<T>& w,
 // pressure jumps of ~1e9 Pa).
 __host__ __device__ __forceinline__ void weno5_js(double a, double b, double c, double d, double e, const WenoK<double>& K, double& fl, double& fr) {
   const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
-  const double m0 = w.s1 * w.s2, m1 = w.s0 * w.s2, m2 = w.s0 * w.s1;
-  const double a0 = m0 * m0, a1 = m1 * m1, a2 = m2 * m2;
-  const double X = a0 * w.A, Y = a2 * w.B;
-  const double dl = K.p3 * a2 + (K.p6 * a1 + a0), dr = K.p3 * a0 + (K.p6 * a1 + a2);
-  const double inv = fast_rcp(dl * dr);
-  weno_values(c, w, K, X + K.p15 * Y, dr * inv, Y + K.p15 * X, dl * inv, fl, fr);
+  const double t0 = w.s0 * w.s0, t1 = w.s1 * w.s1, t2 = w.s2 * w.s2;
+  const double a0 = t1 * t2, a1 = t0 * t2, a2 = t0 * t1;
+  weno_shared(c, w, K, a0, a1, a2, fl, fr);
 }
 
-// FP32: weighted sums of the candidates, each rounding as it always has been.  Squared indicators overflow float for
+// FP32: weighted sums of the candidates' corrections, in the order of operations
+// that defines the FP32 form's rounding.  Squared indicators overflow float for
 // pressure jumps of a few GPa (s ~ 1e19, s^2 > 3.4e38), so the weights are
 // formed from the ratios s_min/s_k in (0, 1] (hardware reciprocals, ~1 ulp):
 // a_k = (s_min/s_k)^2 is d_k/(eps + beta_k)^2 up to the common factor s_min^2,
@@ -390,10 +404,7 @@ __host__ __device__ __forceinline__ void weno5_z(double a, double b, double c, d
   const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
   const double tau = fabs(w.s0 - w.s2);
   const double a0 = (w.s0 + tau) * (w.s1 * w.s2), a1 = (w.s1 + tau) * (w.s0 * w.s2), a2 = (w.s2 + tau) * (w.s0 * w.s1);
-  const double X = a0 * w.A, Y = a2 * w.B;
-  const double dl = K.p3 * a2 + (K.p6 * a1 + a0), dr = K.p3 * a0 + (K.p6 * a1 + a2);
-  const double inv = fast_rcp(dl * dr);
-  weno_values(c, w, K, X + K.p15 * Y, dr * inv, Y + K.p15 * X, dl * inv, fl, fr);
+  weno_shared(c, w, K, a0, a1, a2, fl, fr);
 }
 
 // FP32 WENO5-Z: products of s's would overflow float for pressure-sized data,
@@ -509,8 +520,8 @@ __host__ __device__ __forceinline__ void weno_m_map(double w, double dk, double&
 __host__ __device__ __forceinline__ void weno5_m(double a, double b, double c, double d, double e, const WenoK<double>& K,
                                                  double& fl, double& fr) {
   const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
-  const double m0 = w.s1 * w.s2, m1 = w.s0 * w.s2, m2 = w.s0 * w.s1;
-  const double p0 = m0 * m0, p1 = m1 * m1, p2 = m2 * m2;
+  const double t0 = w.s0 * w.s0, t1 = w.s1 * w.s1, t2 = w.s2 * w.s2;
+  const double p0 = t1 * t2, p1 = t0 * t2, p2 = t0 * t1;
   const double w1 = 0.6 * p1;
   const double wl0 = 0.1 * p0, wl2 = 0.3 * p2;
   const double wr0 = 0.1 * p2, wr2 = 0.3 * p0;
@@ -529,8 +540,9 @@ __host__ __device__ __forceinline__ void weno5_m(double a, double b, double c, d
   const double el0 = nl0 * (ql1 * ql2), el1 = nl1 * (ql0 * ql2), el2 = nl2 * (ql0 * ql1);
   const double er0 = nr0 * (qr1 * qr2), er1 = nr1 * (qr0 * qr2), er2 = nr2 * (qr0 * qr1);
   const double hl = el0 + el1 + el2, hr = er0 + er1 + er2;
-  const double inv2 = fast_rcp(hl * hr);
-  weno_values(c, w, K, el0 * w.A + 0.5 * (el2 * w.B), hr * inv2, er0 * w.B + 0.5 * (er2 * w.A), hl * inv2, fl, fr);
+  // (the mapped weights hold their d_k)
+  const double inv2 = fast_rcp(K.p3 * (hl * hr));
+  weno_values(c, w, K, el0, el1, el2 + el2, hr * inv2, er0, er1, er2 + er2, hl * inv2, fl, fr);
 }
 
 // FP32 WENO5-M: the JS weights of the float weno5_js (ratios s_min/s_k, so

@@ -256,7 +256,12 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
     for (int v = 0; v < NEQ; ++v) {
       const Real f0 = s4[v * LW + own], f1 = so[v * LW + own];
       weno5<WV>(f0, f1, w[0][v], w[1][v], w[2][v], K, WLn[v], WR[v]);
-      if constexpr (kF64) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (kF64) {
+        // formed here: moved to its use behind the face solver it would keep its
+        // six inputs alive instead (30 registers more, and spills)
+        asm volatile("" : "+v"(WLn[v]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     Real F[NEQ], uf;
     if constexpr ((RS & RS_THORNBER) != 0) thornber<NF, D, 1, Real>(pm, WLp, WR);

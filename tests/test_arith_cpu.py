@@ -1,0 +1,96 @@
+"""The double per-cell and per-face arithmetic of csrc/device.h, compiled for the
+CPU with the fused multiply-adds of the device build, against the same formulas in
+80-bit floating point (64-bit mantissa).
+
+The parity tests measure a row against its largest value.  Here every value is
+measured on its own scale, which is what a trace phase beside an interface needs.
+"""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LD = np.longdouble
+EPS64 = 2.0 ** -53
+JS, Z, M = 0, 1, 3
+
+
+@pytest.fixture(scope="session")
+def arith(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    so = str(tmp_path_factory.mktemp("arith") / "arith_host.so")
+    subprocess.run([hipcc, "--offload-host-only", "-x", "hip", "-O2", "-std=c++17", "-mfma", "-fPIC", "-shared",
+                    os.path.join(HERE, "native", "arith_host.hip"), "-o", so], check=True, capture_output=True)
+    return ctypes.CDLL(so)
+
+
+def _ptr(a):
+    assert a.dtype == np.float64 and a.flags.c_contiguous
+    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+
+
+def weno(lib, variant, f, eps=1e-6):
+    f = np.ascontiguousarray(f)
+    fl, fr = np.empty(f.shape[1]), np.empty(f.shape[1])
+    lib.arith_weno(variant, ctypes.c_double(eps), f.shape[1], _ptr(f), _ptr(fl), _ptr(fr))
+    return fl, fr
+
+
+def weno_exact(variant, f, eps=1e-6):
+    """Left-biased value at the face above the centre, in 80 bits; each candidate
+    as the centre value plus its correction."""
+    a, b, c, d, e = (x.astype(LD) for x in f)
+    D0, D1, D2, D3 = b - a, c - b, d - c, e - d
+    beta = [LD(13) / 12 * (D1 - D0) ** 2 + LD(1) / 4 * (3 * D1 - D0) ** 2,
+            LD(13) / 12 * (D2 - D1) ** 2 + LD(1) / 4 * (D1 + D2) ** 2,
+            LD(13) / 12 * (D3 - D2) ** 2 + LD(1) / 4 * (D3 - 3 * D2) ** 2]
+    lin = [LD(1) / 10, LD(6) / 10, LD(3) / 10]
+    if variant == Z:
+        tau = abs(beta[0] - beta[2])
+        w = [g * (1 + tau / (x + LD(eps))) for g, x in zip(lin, beta)]
+    else:
+        w = [g / (LD(eps) + x) ** 2 for g, x in zip(lin, beta)]
+    if variant == M:
+        t = w[0] + w[1] + w[2]
+        w = [x / t for x in w]
+        w = [x * (g + g * g - 3 * g * x + x * x) / (g * g + x * (1 - 2 * g)) for g, x in zip(lin, w)]
+    t = w[0] + w[1] + w[2]
+    parts = [w[0] * (5 * D1 - 2 * D0) / (6 * t), w[1] * (D1 + 2 * D2) / (6 * t), w[2] * (4 * D2 - D3) / (6 * t)]
+    return c + (parts[0] + parts[1] + parts[2]), parts
+
+
+# small smooth side, other side: pressure, a trace partial density, a volume
+# fraction at its floor, a gas density
+JUMPS = [(1e5, 7e8), (1e-3, 1e3), (1e-6, 0.5), (0.125, 1.0)]
+
+
+def jump_stencils(small, large, cut, m=20000, seed=0):
+    """Stencils with `small` (1 +- 5 %, smooth) in the cells before `cut` and `large` in the others."""
+    rng = np.random.default_rng(seed)
+    x0, k = rng.uniform(0, 6, m), rng.uniform(0.01, 0.3, m)
+    f = np.stack([(small if i < cut else large) * (1 + 0.05 * np.sin(x0 + i * k)) for i in range(5)])
+    return np.ascontiguousarray(f)
+
+
+@pytest.mark.parametrize("cut", (3, 4))
+@pytest.mark.parametrize("small,large", JUMPS)
+@pytest.mark.parametrize("variant", (JS, Z, M))
+def test_weno_beside_a_jump_on_the_scale_of_the_value(arith, variant, small, large, cut):
+    """The value at a face on the small, smooth side of a jump.  Bar: the sum of a
+    centre value and three weighted corrections, each formed in at most ten
+    roundings (differences, indicator, its square, weight, normalization, sum), so
+    10 eps of the terms' magnitudes; the centre and the jump's own term, where its
+    weight leaves it any, included."""
+    f = jump_stencils(small, large, cut)
+    got = weno(arith, variant, f)[0]
+    mirrored = weno(arith, variant, f[::-1])[1]
+    ref, parts = weno_exact(variant, f)
+    size = abs(f[2].astype(LD)) + sum(abs(p) for p in parts)
+    for y in (got, mirrored):
+        err = np.abs((y.astype(LD) - ref) / size).astype(float)
+        print(f"variant {variant} {small:g} | {large:g}, {cut} small cells: rms {np.sqrt((err ** 2).mean()):.1e} max {err.max():.1e}")
+        assert err.max() <= 10 * 2 * EPS64
