@@ -130,41 +130,43 @@ __host__ __device__ __forceinline__ void prim_to_cons_vjp(const Params& pm, cons
 // five values; the centre value itself also collects gL + gR (both values are
 // the centre plus a function of the differences).
 //
-// WENO5-JS, in the forms of weno5_js: per side the value is c +- (h - t)/3 with
-// t the weighted third differences over their normalization, t_L = b_0 A + 3/2
-// b_2 B with weights b_k = a_k/n_L (b_0 + 6 b_1 + 3 b_2 = 1), t_R its mirror
-// image.  a_k ~ s_k^-2, so dt_L/ds_0 = -2 b_0 (A - t_L)/s_0, dt_L/ds_1 = 12 b_1
-// t_L/s_1, dt_L/ds_2 = -2 b_2 (3/2 B - 3 t_L)/s_2; the quadratic forms s_k give
-// the differences.  Both sides share the indicators and their derivatives (the
-// two one-sided adjoints of a face formed them twice).
+// WENO5-JS, in the forms of weno5_js: per side the value is c +- the sum of the
+// weighted corrections, y = sum_k w_k c_k with w = (a_0, 6 a_1, 3 a_2)/n_L and
+// c = (l_0, l_1, 2 l_2)/3 on the left, the mirror image on the right.  a_k ~
+// s_k^-2, so dy/ds_k = -2 w_k (c_k - y)/s_k; the sums of squares s_k give the
+// differences.  A correction less the sum keeps its accuracy beside a jump, where
+// the weights of the stencils across it are 1e-12 and less; taken from the third
+// differences instead, 1/s_k of the smooth stencil multiplies the rounding of the
+// jump (1e5 Pa beside 7e8: 1.5e-8 of the derivative, here 3e-16).  Both sides
+// share the indicators and their derivatives.
 __host__ __device__ __forceinline__ void weno_js_centre_vjp(double a, double b, double c, double d, double e,
                                                             const WenoK<double>& K, double gL, double gR, double* gD) {
-  const double D0 = b - a, D3 = e - d;
   const WenoParts<double> w = weno_parts(a, b, c, d, e, K);
-  const double D1 = w.D1, D2 = w.D2;
-  const double A = (D0 + D2) - 2.0 * D1, B = (D1 + D3) - 2.0 * D2;
+  const double D0 = w.D0, D1 = w.D1, D2 = w.D2, D3 = w.D3;
   const double m0 = w.s1 * w.s2, m1 = w.s0 * w.s2, m2 = w.s0 * w.s1;
   const double a0 = m0 * m0, a1 = m1 * m1, a2 = m2 * m2;
   const double dl = K.p3 * a2 + (K.p6 * a1 + a0), dr = K.p3 * a0 + (K.p6 * a1 + a2);
-  const double inv = fast_rcp(dl * dr);
-  const double il = dr * inv, ir = dl * inv;
+  const double inv = fast_rcp(K.p3 * (dl * dr));
+  const double il = dr * inv, ir = dl * inv;  // a third of the inverse normalizations
   const double rP = fast_rcp(w.s0 * m0);
-  const double l0 = a0 * il, l1 = a1 * il, l2 = a2 * il;
-  const double r0 = a0 * ir, r1 = a1 * ir, r2 = a2 * ir;
-  const double A15 = 1.5 * A, B15 = 1.5 * B;
-  const double tl = l0 * A + l2 * B15, tr = r2 * B + r0 * A15;
-  // cotangents: t_L = -gL/3, t_R = gR/3, h_L = gL/3, h_R = -gR/3
-  const double gl = (1.0 / 3.0) * gL, gr = (1.0 / 3.0) * gR;
-  const double L0 = gl * l0, L2 = gl * l2, R0 = gr * r0, R2 = gr * r2;
-  const double tl3 = K.p3 * tl, tr3 = K.p3 * tr;
-  const double g0 = 2.0 * (L0 * (A - tl) - R0 * (A15 - tr3)) * (m0 * rP);
-  const double g1 = 12.0 * (gr * (r1 * tr) - gl * (l1 * tl)) * (m1 * rP);
-  const double g2 = 2.0 * (L2 * (B15 - tl3) - R2 * (B - tr)) * (m2 * rP);
-  const double gA = 1.5 * R0 - L0, gB = R2 - 1.5 * L2;
-  gD[0] = gA + g0 * (2.0 * D0 + (-2.75) * D1);
-  gD[1] = (gB - 2.0 * gA) + (0.5 * gl - gr) + (g0 * (5.0 * D1 + (-2.75) * D0) + g1 * (2.0 * D1 + (-1.25) * D2));
-  gD[2] = (gA - 2.0 * gB) + (gl - 0.5 * gr) + (g2 * (5.0 * D2 + (-2.75) * D3) + g1 * (2.0 * D2 + (-1.25) * D1));
-  gD[3] = gB + g2 * (2.0 * D3 + (-2.75) * D2);
+  const double l0 = K.p25 * D1 - D0, l1 = D2 + 0.5 * D1, l2 = D2 + K.m025 * D3;
+  const double r0 = K.p25 * D2 - D3, r1 = D1 + 0.5 * D2, r2 = D1 + K.m025 * D0;
+  // y = sum_k x_k l_k on the left (yl: three times that); z_k by stencil on the right
+  const double x0 = a0 * il, x1 = K.p6 * (a1 * il), x2 = K.p6 * (a2 * il);
+  const double z2 = a2 * ir, z1 = K.p6 * (a1 * ir), z0 = K.p6 * (a0 * ir);
+  const double yl = K.p3 * (x2 * l2 + (x1 * l1 + x0 * l0)), yr = K.p3 * (z0 * r2 + (z1 * r1 + z2 * r0));
+  const double X0 = gL * x0, X1 = gL * x1, X2 = gL * x2, Z0 = gR * z0, Z1 = gR * z1, Z2 = gR * z2;
+  // cotangents of the s_k: w_k (c_k - y) is x_k (l_k - yl), for k = 2 (on the right
+  // for stencil 0) x_2 (l_2 - yl/2)
+  const double g0 = 2.0 * (Z0 * (r2 - 0.5 * yr) - X0 * (l0 - yl)) * (m0 * rP);
+  const double g1 = 2.0 * (Z1 * (r1 - yr) - X1 * (l1 - yl)) * (m1 * rP);
+  const double g2 = 2.0 * (Z2 * (r0 - yr) - X2 * (l2 - 0.5 * yl)) * (m2 * rP);
+  const double G0 = 2.0 * (g0 * w.u0), G1 = 2.0 * (g1 * w.u1), G2 = 2.0 * (g2 * w.u2);
+  const double q = 2.0 * K.p0609375;
+  gD[0] = G0 - (X0 + K.m025 * Z0);
+  gD[1] = (K.p25 * X0 + (0.5 * X1 - (Z1 + Z0))) + (G1 + (K.m1375 * G0 + q * (g0 * D1)));
+  gD[2] = ((X1 + X2) - (K.p25 * Z2 + 0.5 * Z1)) + (K.m0625 * G1 + (K.m1375 * G2 + q * ((g1 + g2) * D2)));
+  gD[3] = G2 + (Z2 + K.m025 * X2);
 }
 
 // Adjoint of the left-biased WENO5-Z value (Sec. 4.2.2) in the same difference

@@ -1,5 +1,6 @@
-// The double arithmetic of csrc/device.h compiled for the CPU, with the fused
+// The double arithmetic of csrc/device.h and adjoint.h compiled for the CPU, with the fused
 // multiply-adds of the device build, behind plain arrays: tests/test_arith_cpu.py.
+#include "../../paper_2503_07953_amd/csrc/adjoint.h"
 #include "../../paper_2503_07953_amd/csrc/device.h"
 
 using namespace mfc;
@@ -18,6 +19,17 @@ void arith_weno(int variant, double eps, int m, const double* f, double* fl, dou
       weno5_m(a, b, c, d, e, K, fl[i], fr[i]);
     else
       weno5_js(a, b, c, d, e, K, fl[i], fr[i]);
+  }
+}
+
+// WENO5-JS adjoint of m centres: cotangents gL, gR of both values to those of the
+// four differences (gD: four rows of m).
+void arith_weno_js_vjp(double eps, int m, const double* f, const double* gL, const double* gR, double* gD) {
+  const WenoK<double> K = weno_consts(eps);
+  for (int i = 0; i < m; ++i) {
+    double g[4];
+    weno_js_centre_vjp(f[i], f[m + i], f[2 * m + i], f[3 * m + i], f[4 * m + i], K, gL[i], gR[i], g);
+    for (int k = 0; k < 4; ++k) gD[k * m + i] = g[k];
   }
 }
 

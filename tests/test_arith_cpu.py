@@ -1,4 +1,4 @@
-"""The double per-cell and per-face arithmetic of csrc/device.h, compiled for the
+"""The double per-cell and per-face arithmetic of csrc/device.h and adjoint.h, compiled for the
 CPU with the fused multiply-adds of the device build, against the same formulas in
 80-bit floating point (64-bit mantissa).
 
@@ -94,3 +94,54 @@ def test_weno_beside_a_jump_on_the_scale_of_the_value(arith, variant, small, lar
         err = np.abs((y.astype(LD) - ref) / size).astype(float)
         print(f"variant {variant} {small:g} | {large:g}, {cut} small cells: rms {np.sqrt((err ** 2).mean()):.1e} max {err.max():.1e}")
         assert err.max() <= 10 * 2 * EPS64
+
+
+def js_derivative(f, eps=1e-6):
+    """d(left-biased WENO5-JS value)/dD_j in 80 bits, and the sum of the magnitudes of the terms that make it up."""
+    a, b, c, d, e = (x.astype(LD) for x in f)
+    D = [b - a, c - b, d - c, e - d]
+    corr = [(5 * D[1] - 2 * D[0]) / 6, (D[1] + 2 * D[2]) / 6, (4 * D[2] - D[3]) / 6]
+    dcorr = np.array([[-2, 5, 0, 0], [0, 1, 2, 0], [0, 0, 4, -1]], LD) / 6
+    # beta_k as quadratic forms of the differences: 13/12 u^2 + 1/4 v^2
+    uv = [((-1, 1, 0, 0), (-1, 3, 0, 0)), ((0, -1, 1, 0), (0, 1, 1, 0)), ((0, 0, -1, 1), (0, 0, -3, 1))]
+    dot = lambda w: sum(LD(x) * y for x, y in zip(w, D))
+    beta = [LD(13) / 12 * dot(u) ** 2 + LD(1) / 4 * dot(v) ** 2 for u, v in uv]
+    w = [g / (LD(eps) + x) ** 2 for g, x in zip((LD(1) / 10, LD(6) / 10, LD(3) / 10), beta)]
+    t = w[0] + w[1] + w[2]
+    w = [x / t for x in w]
+    y = w[0] * corr[0] + w[1] * corr[1] + w[2] * corr[2]
+    out, size = [], []
+    for j in range(4):
+        g, m = 0, 0
+        for k in range(3):
+            u, v = uv[k]
+            db = LD(13) / 6 * dot(u) * u[j] + LD(1) / 2 * dot(v) * v[j]
+            mag = sum(abs(LD(13) / 6 * u[i] * u[j] + LD(1) / 2 * v[i] * v[j]) * abs(D[i]) for i in range(4))
+            r = 2 * w[k] / (LD(eps) + beta[k])
+            g = g + w[k] * dcorr[k, j] - r * (corr[k] - y) * db
+            m = m + w[k] * abs(dcorr[k, j]) + r * (abs(corr[k]) + abs(y)) * mag
+        out.append(g)
+        size.append(m)
+    return out, size
+
+
+@pytest.mark.parametrize("cut", (1, 2, 3, 4, 5))
+@pytest.mark.parametrize("small,large", JUMPS)
+def test_weno_js_adjoint_beside_a_jump(arith, small, large, cut):
+    """The derivative of both biased values in the four differences, each entry
+    against the magnitudes of the terms that make it up (the largest entry of the
+    stencil where its own are smaller: one difference's entry holds a share of its
+    neighbours' weights).  Bar: 30 roundings."""
+    f = jump_stencils(small, large, cut, seed=1)
+    m = f.shape[1]
+    ref, size = js_derivative(f)
+    top = np.maximum.reduce(size)
+    one, zero = np.ones(m), np.zeros(m)
+    gD = np.empty((4, m))
+    arith.arith_weno_js_vjp(ctypes.c_double(1e-6), m, _ptr(f), _ptr(one), _ptr(zero), _ptr(gD))
+    left = [np.abs((gD[j].astype(LD) - ref[j]) / top).max() for j in range(4)]
+    g = np.ascontiguousarray(f[::-1])
+    arith.arith_weno_js_vjp(ctypes.c_double(1e-6), m, _ptr(g), _ptr(zero), _ptr(one), _ptr(gD))
+    right = [np.abs((-gD[3 - j].astype(LD) - ref[j]) / top).max() for j in range(4)]
+    print(f"{small:g} | {large:g}, {cut} small cells: {float(max(left)):.1e} {float(max(right)):.1e}")
+    assert max(max(left), max(right)) <= 30 * 2 * EPS64
