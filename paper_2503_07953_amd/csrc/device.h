@@ -49,15 +49,13 @@ struct Params {
 //   NU_DL + r: at the left face (xi = -1/2);
 //   NU_INVW: 1/h of the cell at that position;
 // and the same reconstruction in the form that the double kernels evaluate:
-//   NU_B + 3 r (+1, +2): beta_r = D_r (b_0 D_r + b_1 D_{r+1}) + b_2 D_{r+1}^2;
-//   NU_A (+1): third difference A = D_2 + a_0 D_0 + a_1 D_1 of the first four cells;
-//   NU_C (+1): B = D_1 + a_0 D_3 + a_1 D_2 of the last four;
-//   NU_KR (+1), NU_KL (+1): ideal weight of candidate 0 (2) times its value less
-//   candidate 1's per A (B), at the right and the left face;
-//   NU_QR (+1), NU_QL (+1): candidate 1's value less f_2, per D_1 and D_2.
+//   NU_B + 3 r (+1, +2): beta_r = (b_0 D + b_1 D')^2 + b_2 D'^2, D and D' the
+//   candidate's two differences: (D_0, D_1), (D_1, D_2) and (D_3, D_2);
+//   NU_VR + 2 r (+1), NU_VL + 2 r (+1): candidate r's value less f_2, per D_r and
+//   D_{r+1}, times its ideal weight, at the right and the left face.
 enum {
   NU_MU0 = 0, NU_M1 = 6, NU_M2 = 12, NU_DR = 18, NU_DL = 21, NU_INVW = 24,
-  NU_B = 25, NU_A = 34, NU_C = 36, NU_KR = 38, NU_KL = 40, NU_QR = 42, NU_QL = 44, kNuCoefs = 46
+  NU_B = 25, NU_VR = 34, NU_VL = 40, kNuCoefs = 46
 };
 
 // 1/h of cell i along axis d (uniform or tabulated).
@@ -602,12 +600,12 @@ struct NuK {
   static constexpr int kCount = (sizeof(T) == 8 ? (int)kNuCoefs : (int)NU_DR) - kFirst;
   T k[kCount];
   T w[6];  // NU_DR, NU_DL
-  __device__ __forceinline__ T operator()(int row) const {
+  __host__ __device__ __forceinline__ T operator()(int row) const {
     return (row >= NU_DR && row < NU_INVW) ? w[row - NU_DR] : k[row - kFirst];
   }
 };
 template <typename T>
-__device__ __forceinline__ NuK<T> nu_entry(const Params& pm, int d, int c) {
+__host__ __device__ __forceinline__ NuK<T> nu_entry(const Params& pm, int d, int c) {
   const long long st = (long long)pm.n[d] + 6;
   const T* cf;
   if constexpr (sizeof(T) == 8)
@@ -623,33 +621,39 @@ __device__ __forceinline__ NuK<T> nu_entry(const Params& pm, int d, int c) {
 }
 
 // Double: the weights d_r/(eps + beta_r)^2 over the common denominator, both
-// normalizations from one refined reciprocal (as weno5_js), and the third-
-// difference form: candidates 0 and 2 differ from candidate 1 by multiples of A
-// and B, so none is formed: 52 operations a centre and row instead of 78, and the
-// z pass issues 744 instructions instead of 902.  With the entry read ahead of the
-// tile's loads a 128 x 96 x 80 two-fluid RHS takes 154 us instead of 165 (these
-// passes hold 54 registers of coefficients and run four waves per SIMD; a 160^3
-// one 570 instead of 644).  Against long double its error is that of the sum of
-// candidates on smooth data and 1.3 times on random data (8e-17 rms of the
-// largest value), stretching up to 2:1.
-__device__ __forceinline__ void weno5_nu(double a, double b, double c, double d, double e, double eps,
-                                         const NuK<double>& k, double& fr, double& fl) {
+// normalizations from one refined reciprocal (as weno5_js); the indicators as sums
+// of squares and the candidates with their ideal weights folded in: 57 operations a
+// centre and row instead of 78 from m0, m1 and m2.  Each candidate is weighted on
+// its own, so that the value beside a jump keeps its accuracy, as in weno_values.
+// On random data the evaluation's error against long double is 5.4e-17 rms of the
+// terms (from m0, m1 and m2 4.9e-17) for widths to 10:1; with the table's own
+// rounding both are 4.9e-16 at 1.2:1, 5.5e-16 at 2:1 and 3.8e-15 at 10:1.
+// (These passes hold 54 registers of coefficients and run four waves per SIMD.)
+__host__ __device__ __forceinline__ void weno5_nu(double a, double b, double c, double d, double e, double eps,
+                                                  const NuK<double>& k, double& fr, double& fl) {
   const double D0 = b - a, D1 = c - b, D2 = d - c, D3 = e - d;
   const double P1 = D1 * D1, P2 = D2 * D2;
-  const double s0 = D0 * (k(NU_B) * D0 + k(NU_B + 1) * D1) + (k(NU_B + 2) * P1 + eps);
-  const double s1 = D1 * (k(NU_B + 3) * D1 + k(NU_B + 4) * D2) + (k(NU_B + 5) * P2 + eps);
-  const double s2 = D3 * (k(NU_B + 8) * D3 + k(NU_B + 7) * D2) + (k(NU_B + 6) * P2 + eps);
-  const double A = k(NU_A) * D0 + (k(NU_A + 1) * D1 + D2);
-  const double B = k(NU_C) * D3 + (k(NU_C + 1) * D2 + D1);
-  const double m0 = s1 * s2, m1 = s0 * s2, m2 = s0 * s1;
-  const double p0 = m0 * m0, p1 = m1 * m1, p2 = m2 * m2;
-  const double X = p0 * A, Y = p2 * B;
-  const double sr = k(NU_DR) * p0 + (k(NU_DR + 1) * p1 + k(NU_DR + 2) * p2);
-  const double sl = k(NU_DL) * p0 + (k(NU_DL + 1) * p1 + k(NU_DL + 2) * p2);
-  const double nr = k(NU_KR) * X + k(NU_KR + 1) * Y, nl = k(NU_KL) * X + k(NU_KL + 1) * Y;
+  const double u0 = k(NU_B) * D0 + k(NU_B + 1) * D1, u1 = k(NU_B + 3) * D1 + k(NU_B + 4) * D2,
+               u2 = k(NU_B + 6) * D3 + k(NU_B + 7) * D2;
+  const double s0 = u0 * u0 + (k(NU_B + 2) * P1 + eps), s1 = u1 * u1 + (k(NU_B + 5) * P2 + eps),
+               s2 = u2 * u2 + (k(NU_B + 8) * P2 + eps);
+  const double t0 = s0 * s0, t1 = s1 * s1, t2 = s2 * s2;
+  const double p0 = t1 * t2;
+  double nr = p0 * (k(NU_VR) * D0 + k(NU_VR + 1) * D1), nl = p0 * (k(NU_VL) * D0 + k(NU_VL + 1) * D1);
+  double sr = k(NU_DR) * p0, sl = k(NU_DL) * p0;
+  const double p2 = t0 * t1;
+  nr += p2 * (k(NU_VR + 4) * D2 + k(NU_VR + 5) * D3);
+  nl += p2 * (k(NU_VL + 4) * D2 + k(NU_VL + 5) * D3);
+  sr += k(NU_DR + 2) * p2;
+  sl += k(NU_DL + 2) * p2;
+  const double p1 = t0 * t2;
+  nr += p1 * (k(NU_VR + 2) * D1 + k(NU_VR + 3) * D2);
+  nl += p1 * (k(NU_VL + 2) * D1 + k(NU_VL + 3) * D2);
+  sr += k(NU_DR + 1) * p1;
+  sl += k(NU_DL + 1) * p1;
   const double inv = fast_rcp(sr * sl);
-  fr = c + (nr * (sl * inv) + (k(NU_QR) * D1 + k(NU_QR + 1) * D2));
-  fl = c + (nl * (sr * inv) + (k(NU_QL) * D1 + k(NU_QL + 1) * D2));
+  fr = c + nr * (sl * inv);
+  fl = c + nl * (sr * inv);
 }
 
 // Float: the weights from the ratios s_min/s_r, s_r = eps + beta_r (as the

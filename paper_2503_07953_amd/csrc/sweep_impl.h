@@ -367,9 +367,10 @@ __global__ __launch_bounds__((Tile<DIR, D, Real>::NT)) void sweep_kernel(Params 
         weno5_nu(f0, f1, f2, f3, f4, K.eps, KN, WLc[v], WRc[v]);
       else
         weno5<WV>(f0, f1, f2, f3, f4, K, WLc[v], WRc[v]);
-      // formed here, not at its use behind the barrier, where its inputs would
-      // have to wait in three times the registers
-      if constexpr (!kLaneX && sizeof(Real) == 8) asm volatile("" : "+v"(WLc[v]));
+      // formed here, not where it is used, behind the barrier (or, with tabulated
+      // coefficients, the lanes' exchange): its inputs would have to wait there in
+      // three times the registers
+      if constexpr ((!kLaneX || WV == kWvNonUniform) && sizeof(Real) == 8) asm volatile("" : "+v"(WLc[v]));
     }
     if constexpr (NF == 2) {
       alpha_cell[0] = sh[lds_index<DIR, D, Real>(R::ALPHA, a + 2, b)];

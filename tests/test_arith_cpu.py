@@ -145,3 +145,68 @@ def test_weno_js_adjoint_beside_a_jump(arith, small, large, cut):
     right = [np.abs((-gD[3 - j].astype(LD) - ref[j]) / top).max() for j in range(4)]
     print(f"{small:g} | {large:g}, {cut} small cells: {float(max(left)):.1e} {float(max(right)):.1e}")
     assert max(max(left), max(right)) <= 30 * 2 * EPS64
+
+
+def nu_exact(base, f, eps):
+    """Both face values of the tabulated scheme in 80 bits from the table's candidates
+    and ideal weights, and the magnitudes of their terms: [right, left]."""
+    D = [f[i + 1].astype(LD) - f[i].astype(LD) for i in range(4)]
+    b = base.astype(LD)
+    lin = lambda row, r: (b[row + 2 * r] * D[r], b[row + 2 * r + 1] * D[r + 1])
+    m0, m1, m2 = ([lin(row, r) for r in range(3)] for row in (0, 6, 12))
+    beta = [sum(m1[r]) ** 2 + LD(13) / 3 * sum(m2[r]) ** 2 for r in range(3)]
+    out = []
+    for row, sign in ((18, 1), (21, -1)):
+        w = [b[row + r] / (LD(eps) + beta[r]) ** 2 for r in range(3)]
+        t = w[0] + w[1] + w[2]
+        y = sum(w[r] * (sum(m0[r]) + sum(m2[r]) / 4 + sign * sum(m1[r]) / 2) for r in range(3)) / t
+        mag = sum(abs(w[r]) * sum(abs(m0[r][j]) + abs(m2[r][j]) / 4 + abs(m1[r][j]) / 2 for j in (0, 1)) for r in range(3))
+        out.append((f[2].astype(LD) + y, abs(f[2].astype(LD)) + mag / abs(t)))
+    return out
+
+
+@pytest.mark.parametrize("kind", ("smooth", "random", "jump"))
+@pytest.mark.parametrize("ratio", (1.2, 2.0, 10.0))
+def test_weno_on_a_stretched_grid_on_the_scale_of_the_value(arith, ratio, kind):
+    """The folded table entries against the candidates and ideal weights that they
+    come from, widths within `ratio` of each other, smooth and random data and both
+    sides of jumps.  Bar: 10 eps of the magnitudes of the terms, as on a uniform
+    grid."""
+    rng = np.random.default_rng(5)
+    worst, sq, count = 0.0, 0.0, 0
+    for g in range(60):
+        widths = ratio ** rng.uniform(-0.5, 0.5, 5)
+        faces = np.concatenate([[0.0], np.cumsum(widths)])
+        x = np.cumsum(widths)[:, None] - 0.5 * widths[:, None]
+        m = 400
+        smooth = 1 + 0.05 * np.sin(rng.uniform(0, 6, m) + 10 ** rng.uniform(-2, 0, m) * x)
+        if kind == "smooth":
+            f = smooth
+        elif kind == "random":
+            f = rng.uniform(-1, 1, (5, m))
+        else:
+            small, large = JUMPS[g % 4]
+            f = smooth * np.where(np.arange(5)[:, None] < rng.integers(1, 5, m), small, large)
+            f = f if g % 2 else f[::-1]
+        f = np.ascontiguousarray(f)
+        fl, fr, base = np.empty(m), np.empty(m), np.empty(24)
+        assert arith.arith_weno_nu(ctypes.c_double(1e-6), _ptr(faces), m, _ptr(f), _ptr(fl), _ptr(fr), _ptr(base)) == 0
+        for got, (ref, size) in zip((fl, fr), nu_exact(base, f, 1e-6)):  # fl: the right face
+            e = np.abs((got.astype(LD) - ref) / size).astype(float)
+            worst, sq, count = max(worst, e.max()), sq + (e ** 2).sum(), count + m
+    print(f"{kind}, widths to {ratio}: rms {np.sqrt(sq / count):.1e} max {worst:.1e}")
+    assert worst <= 10 * 2 * EPS64
+
+
+def test_weno_on_extremely_stretched_grids_stays_finite(arith):
+    """Cells up to 1e12 times their neighbours: the folded entries are products, none a quotient that may have no divisor."""
+    rng = np.random.default_rng(6)
+    f = np.ascontiguousarray(rng.uniform(-1, 1, (5, 100)))
+    for ratio in (1e3, 1e6, 1e12):
+        for _ in range(20):
+            faces = np.concatenate([[0.0], np.cumsum(ratio ** rng.uniform(-0.5, 0.5, 5))])
+            fl, fr, base = np.empty(100), np.empty(100), np.empty(24)
+            if arith.arith_weno_nu(ctypes.c_double(1e-6), _ptr(faces), 100, _ptr(f), _ptr(fl), _ptr(fr), _ptr(base)):
+                continue
+            if np.isfinite(base).all():
+                assert np.isfinite(fl).all() and np.isfinite(fr).all(), (ratio, faces)
