@@ -810,8 +810,10 @@ __host__ __device__ __forceinline__ bool hllc(const Params& pm, const T* WL, con
   // With m = chi u_f, chi = (S_K - u)/(S_K - S*), u_f = S* and p* = p + rho
   // (S_K - u)(S* - u), the star flux F_K + S_K (U* - U) is U* S* plus the
   // pressure terms of p*: rows rho_i m, rho v m, rho m S* + p* and (E* + p*)
-  // S* with E* = chi E + (p* S* - p u)/(S_K - S*).  Outside the star region
-  // chi = 1, u_f = u and p* = p give the physical flux; (S_K - S*) is
+  // S* with E* = chi E + (p* S* - p u)/(S_K - S*).  The last numerator is (S* - u)
+  // (p + rho (S_K - u) S*), exactly zero outside the star region (p* S* - p u as it
+  // stands leaves the rounding of p u there, added to a pressure).  Outside the star
+  // region chi = 1, u_f = u and p* = p give the physical flux; (S_K - S*) is
   // replaced by 1 there so that a degenerate value cannot poison the flux.
   // Against the difference form of hllc_fp32 this saves the reciprocal of S_K - u
   // and 20 operations a face, and nothing cancels.
@@ -824,7 +826,7 @@ __host__ __device__ __forceinline__ bool hllc(const Params& pm, const T* WL, con
   for (int i = 0; i < NF; ++i) F[i] = W[i] * m;
 #pragma unroll
   for (int e = 0; e < D; ++e) F[R::MOM + e] = (e == DIR) ? rhom * us + ps : rhom * W[R::MOM + e];
-  F[R::E] = (chi * E + ((ps * us - p * un) * r + ps)) * us;
+  F[R::E] = (chi * E + (du * (p + k * us) * r + ps)) * us;
   if constexpr (APC) {
     F[R::MOM + DIR] = F[R::MOM + DIR] + apc_m;
     F[R::E] = F[R::E] + apc_e;

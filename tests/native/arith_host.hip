@@ -5,6 +5,8 @@
 #include "../../paper_2503_07953_amd/csrc/device.h"
 #include "../../paper_2503_07953_amd/csrc/nu_table.h"
 
+#include <type_traits>
+
 using namespace mfc;
 
 extern "C" {
@@ -49,6 +51,46 @@ int arith_weno_nu(double eps, const double* faces, int m, const double* f, doubl
   for (int i = 0; i < m; ++i)
     weno5_nu(f[i], f[m + i], f[2 * m + i], f[3 * m + i], f[4 * m + i], eps, K, fl[i], fr[i]);
   return 0;
+}
+
+// Fluxes and face velocity of m faces of a 2D grid along x with the option bits of
+// `options` (RS_*): rows of m values.  vjp_uf: the face velocity as the adjoint forms it.
+void arith_face(int options, int nf, const double* gamma, const double* pi_inf, int m, const double* wl, const double* wr,
+                double* flux, double* uf, double* vjp_uf) {
+  Params pm = {};
+  for (int i = 0; i < 2; ++i) {
+    const int k = i < nf ? i : 0;
+    pm.G[i] = 1.0 / (gamma[k] - 1.0);
+    pm.P[i] = gamma[k] * pi_inf[k] / (gamma[k] - 1.0);
+  }
+  auto face = [&](auto options_, auto nf_) {
+    constexpr int RS = decltype(options_)::value, NF = decltype(nf_)::value, NEQ = Rows<NF, 2>::NEQ;
+    for (int i = 0; i < m; ++i) {
+      double L[NEQ], R[NEQ], F[NEQ], Fb[NEQ], Lb[NEQ], Rb[NEQ];
+      for (int v = 0; v < NEQ; ++v) {
+        L[v] = wl[v * m + i];
+        R[v] = wr[v * m + i];
+        Fb[v] = 1.0;
+        Lb[v] = Rb[v] = 0.0;
+      }
+      if constexpr ((RS & RS_THORNBER) != 0) thornber<NF, 2, 0, double>(pm, L, R);
+      riemann<RS, NF, 2, 0, double>(pm, L, R, F, uf[i]);
+      riemann_vjp<RS, NF, 2, 0>(pm, L, R, Fb, 1.0, Lb, Rb, &vjp_uf[i]);
+      for (int v = 0; v < NEQ; ++v) flux[v * m + i] = F[v];
+    }
+  };
+  auto fluids = [&](auto options_) {
+    if (nf == 1)
+      face(options_, std::integral_constant<int, 1>());
+    else
+      face(options_, std::integral_constant<int, 2>());
+  };
+  switch (options) {
+    case RS_HLL: fluids(std::integral_constant<int, RS_HLL>()); break;
+    case RS_THORNBER: fluids(std::integral_constant<int, RS_THORNBER>()); break;
+    case RS_APC: fluids(std::integral_constant<int, RS_APC>()); break;
+    default: fluids(std::integral_constant<int, 0>()); break;
+  }
 }
 
 }  // extern "C"
