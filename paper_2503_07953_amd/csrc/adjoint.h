@@ -426,7 +426,7 @@ __device__ __forceinline__ void weno_centre_vjp(double a, double b, double c, do
 // ---------------------------------------------------------------------------
 template <int NF, int D>
 struct SideState {
-  double rho, Gam, Pi, p, un, usq, E, c2, c;
+  double rho, Gam, Pi, p, un, usq, E, c;
 };
 
 template <int NF, int D, int DIR>
@@ -444,8 +444,8 @@ __host__ __device__ __forceinline__ void side_state(const Params& pm, const doub
 #pragma unroll
   for (int e = 0; e < D; ++e) s.usq += W[R::MOM + e] * W[R::MOM + e];
   s.E = s.Gam * s.p + s.Pi + 0.5 * s.rho * s.usq;
-  s.c2 = sound_speed_sq(s.rho, s.p, s.Gam, s.Pi);
-  s.c = sqrt(s.c2);
+  double x;
+  s.c = face_sound_speed(s.rho, s.p, s.Gam, s.Pi, x);
 }
 
 // Cotangents of the side scalars, pushed to the primitive cotangents of that side.
@@ -464,7 +464,7 @@ __host__ __device__ __forceinline__ void side_scalars_vjp(const Params& pm, cons
     const double c2b = 0.5 * cb * fast_rcp(s.c);
     const double rden = fast_rcp(s.Gam * s.rho);
     const double Nb = c2b * rden;
-    const double Db = -c2b * s.c2 * rden;
+    const double Db = -c2b * (s.c * s.c) * rden;
     Gamb += Nb * s.p + Db * s.rho;
     pb += Nb * (s.Gam + 1.0);
     Pib += Nb;
@@ -491,17 +491,10 @@ __host__ __device__ __forceinline__ void hllc_vjp(const Params& pm, const double
   SideState<NF, D> L, Rs;
   side_state<NF, D, DIR>(pm, WL, L);
   side_state<NF, D, DIR>(pm, WR, Rs);
-  const double sla = L.un - L.c, slb = Rs.un - Rs.c, sra = L.un + L.c, srb = Rs.un + Rs.c;
-  const bool sl_left = sla <= slb;
-  const bool sr_left = sra >= srb;
-  const double SL = sl_left ? sla : slb;
-  const double SR = sr_left ? sra : srb;
-  const double aL = SL - L.un, aR = SR - Rs.un;
-  const double num = (Rs.p - L.p) + L.rho * L.un * aL - Rs.rho * Rs.un * aR;
-  // S* = num / den with den = rho_L a_L - rho_R a_R < 0, formed as in the
-  // forward solver: num * -(1 / -den)
-  const double rnd = fast_rcp(Rs.rho * aR - L.rho * aL);
-  const double Sstar = num * -rnd;
+  // the forward solver's waves, bit for bit
+  const HllcWaves w = hllc_waves(L.rho, L.p, L.un, L.c, Rs.rho, Rs.p, Rs.un, Rs.c);
+  const bool sl_left = w.sl_left, sr_left = w.sr_left;
+  const double SL = w.SL, SR = w.SR, aL = w.aL, aR = w.aR, rnd = w.rden, Sstar = w.Sstar;
   const bool useL = (SL >= 0.0) || (Sstar >= 0.0);
   const bool star = useL ? !(SL >= 0.0) : (SR > 0.0);
   // the side K the face takes, selected element by element (no pointer select)
@@ -786,7 +779,7 @@ __host__ __device__ __forceinline__ void hll_vjp(const Params& pm, const double*
     c = SL * SR;
     r = fast_rcp(SR - SL);
   }
-  if (uf_out) *uf_out = (a * L.un + b * Rs.un) * r;
+  if (uf_out) *uf_out = fma(b, Rs.un, a * L.un) * r;
   // per-row physical fluxes and conservative values of both sides
   double FL[NEQ], FR[NEQ], UL[NEQ], UR[NEQ];
 #pragma unroll

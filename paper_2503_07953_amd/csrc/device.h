@@ -96,11 +96,18 @@ __host__ __device__ __forceinline__ int ghost_index(int g, int n, int lo, int hi
 
 // Mixture Gamma = sum alpha_i G_i and Pi = sum alpha_i P_i (Sec. 2.1.1 mixture
 // rules with the stiffened-gas law of Sec. 2.2).  One fluid: alpha = 1.
+// (The double form's fused products are written out here, in cons_to_prim, in
+// face_sound_speed and in hllc_waves: the adjoint's kernels call the same functions,
+// and the last bit of S* picks the side of a face at rest, so that both have to
+// round alike whatever the compiler would fuse around them.)
 template <int NF, typename T>
 __host__ __device__ __forceinline__ void mixture(const Params& pm, T a0, T a1, T& Gam, T& Pi) {
   if constexpr (NF == 1) {
     Gam = T(pm.G[0]);
     Pi = T(pm.P[0]);
+  } else if constexpr (sizeof(T) == 8) {
+    Gam = fma(a0, pm.G[0], a1 * pm.G[1]);
+    Pi = fma(a0, pm.P[0], a1 * pm.P[1]);
   } else {
     Gam = a0 * T(pm.G[0]) + a1 * T(pm.G[1]);
     Pi = a0 * T(pm.P[0]) + a1 * T(pm.P[1]);
@@ -140,7 +147,10 @@ __host__ __device__ __forceinline__ void cons_to_prim(const Params& pm, const do
   for (int d = 0; d < D; ++d) {
     const double u = U[R::MOM + d] * rinv;
     W[R::MOM + d] = u;
-    usq += u * u;
+    if constexpr (sizeof(Real) == 8)
+      usq = fma(u, u, usq);
+    else
+      usq += u * u;
   }
   double Gam, Pi;
   if constexpr (NF == 2)
@@ -215,7 +225,7 @@ __host__ __device__ __forceinline__ double sound_speed_sq(double rho, double p, 
 // finite, and c is NaN for c^2 < 0.
 constexpr double kTinyOffset = 1e-300;
 __host__ __device__ __forceinline__ double face_sound_speed(double rho, double p, double Gam, double Pi, double& x) {
-  const double N = Gam * p + (p + Pi);
+  const double N = fma(Gam, p, p + Pi);
   const double d = Gam * rho;
   x = N * d;
   const double xo = x + kTinyOffset;
@@ -224,9 +234,9 @@ __host__ __device__ __forceinline__ double face_sound_speed(double rho, double p
 #else
   const double y = 1.0 / sqrt(xo);
 #endif
-  const double e = 1.0 - (xo * y) * y;
+  const double e = fma(-(xo * y), y, 1.0);
   const double g = fabs(N) * y;
-  return g + g * (e * (0.5 + 0.375 * e));
+  return fma(g, e * fma(0.375, e, 0.5), g);
 }
 
 // Kapila's K of one cell (Sec. 2.1.1): the alpha_1 row carries
@@ -739,6 +749,30 @@ __device__ __forceinline__ void weno5(T a, T b, T c, T d, T e, const WenoK<T>& K
 //   volume fractions are carried by the contact: flux alpha_K u_f.
 // Returns true when a side has c^2 <= 0 or a flux is not finite.
 // ---------------------------------------------------------------------------
+// The waves of a face, for the solver and its adjoint: a = S_K - u_K, k = rho_K a_K,
+// rden = 1/(k_R - k_L).
+struct HllcWaves {
+  double SL, SR, aL, aR, kL, kR, rden, Sstar;
+  bool sl_left, sr_left;  // which side each estimate took
+};
+__host__ __device__ __forceinline__ HllcWaves hllc_waves(double rhoL, double pL, double uL, double cL, double rhoR,
+                                                         double pR, double uR, double cR) {
+  HllcWaves w;
+  const double sla = uL - cL, slb = uR - cR, sra = uL + cL, srb = uR + cR;
+  w.sl_left = sla <= slb;
+  w.sr_left = sra >= srb;
+  w.SL = w.sl_left ? sla : slb;
+  w.SR = w.sr_left ? sra : srb;
+  w.aL = w.SL - uL;
+  w.aR = w.SR - uR;
+  w.kL = rhoL * w.aL;
+  w.kR = rhoR * w.aR;
+  // the denominator is strictly negative for physical states (S_L < u_L, S_R > u_R)
+  w.rden = fast_rcp(fma(rhoR, w.aR, -w.kL));
+  w.Sstar = fma(-uR, w.kR, fma(uL, w.kL, pR - pL)) * -w.rden;
+  return w;
+}
+
 template <int NF, int D, int DIR, typename T, bool APC = false>
 __host__ __device__ __forceinline__ bool hllc(const Params& pm, const T* WL, const T* WR, T* F, T& uf) {
   using R = Rows<NF, D>;
@@ -762,14 +796,8 @@ __host__ __device__ __forceinline__ bool hllc(const Params& pm, const T* WL, con
   const double cL = face_sound_speed(double(rhoL), double(pL), double(GamL), double(PiL), xL);
   const double cR = face_sound_speed(double(rhoR), double(pR), double(GamR), double(PiR), xR);
   const double dunL = double(unL), dunR = double(unR);
-  const double sla = dunL - cL, slb = dunR - cR, sra = dunL + cL, srb = dunR + cR;
-  const double SL = (sla <= slb) ? sla : slb;
-  const double SR = (sra >= srb) ? sra : srb;
-  const double aL = SL - dunL, aR = SR - dunR;
-  const double kL = double(rhoL) * aL, kR = double(rhoR) * aR;
-  // the denominator is strictly negative for physical states (S_L < u_L, S_R > u_R)
-  const double rden = fast_rcp(kR - kL);
-  const double Sstar = (double(pR) - double(pL) + dunL * kL - dunR * kR) * -rden;
+  const HllcWaves w = hllc_waves(double(rhoL), double(pL), dunL, cL, double(rhoR), double(pR), dunR, cR);
+  const double SL = w.SL, SR = w.SR, kL = w.kL, kR = w.kR, Sstar = w.Sstar, rden = w.rden;
 
   // side the face takes and whether it lies in the star region
   const bool useL = (SL >= 0.0) || (Sstar >= 0.0);
@@ -782,7 +810,7 @@ __host__ __device__ __forceinline__ bool hllc(const Params& pm, const T* WL, con
   const T Pi = useL ? PiL : PiR;
   const double p = double(W[R::E]);
   const double un = double(W[R::MOM + DIR]);
-  const double a = useL ? aL : aR;  // S_K - u
+  const double a = useL ? w.aL : w.aR;  // S_K - u
   const double k = useL ? kL : kR;
 
   T usq = T(0);

@@ -25,8 +25,8 @@
 // positions of every face (48 doubles a face and axis for two fluids in 3D)
 // and a cell pass that gathered them: 2.3 KB per cell through memory, and the
 // indicators of a centre formed four times.  RHS adjoint, two fluids: 96 x 80 x
-// 72 cells 445 -> 199 us, 128^3 1666 -> 701, 256^2 47.5 -> 29.6, 64^2 25.2 ->
-// 21.7.
+// 72 cells 440 -> 184 us, 128^3 1666 -> 677, 256^2 47.5 -> 28.9, 64^2 25.2 ->
+// 20.4.
 //
 // Lanes 3..60 of a wave are outputs (a cell needs the centres two below to two
 // above it and their faces); a line's positions run from -pad to n + pad - 1,
@@ -183,9 +183,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
       }
     }
     if (flip) U[R::MOM + DIR] = -U[R::MOM + DIR];
-    // (in the float form's order of operations: with the double form's a
-    // 96 x 80 x 72 adjoint was 2.1e-11 from its 64-bit reference, with this 1.8e-12)
-    cons_to_prim<NF, D, float>(pm, U, W);
+    cons_to_prim<NF, D, double>(pm, U, W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) sw[(v * TB + bb) * LS + s] = W[v];
   }
@@ -355,8 +353,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
     }
     double Ub[NEQ];
     cons_to_prim_vjp_at_prim<NF, D>(pm, Wc, t, Ub);
-    // qbar, or (epi.stage > 0) the reverse stage combination of v = Ub, the
-    // same operations as launch_adj_stage's
+    // qbar, or (epi.stage > 0) the reverse stage combination of v = Ub
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) {
       const long long e = v * nc + cell;

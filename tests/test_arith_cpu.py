@@ -244,3 +244,27 @@ def test_uniform_stream_in_any_unit_of_velocity(arith, options, mach, unit):
     err = np.abs(flux[3] / ((E + p) * u) - 1).max()
     print(f"options {options} Mach {mach} unit {unit:g}: {float(err):.1e}")
     assert err <= 20 * 2 * EPS64
+
+
+def interface_faces(m, seed, speed):
+    """Two-fluid face states on both sides of smeared interfaces, pressure equal up to its rounding, velocity noise of size `speed`."""
+    rng = np.random.default_rng(seed)
+    w = []
+    p = 1e5 * (1 + 0.1 * rng.uniform(-1, 1, m))
+    for _ in range(2):
+        a = rng.uniform(1e-6, 1 - 1e-6, m)
+        noise = 1 + rng.integers(-2, 3, m) * 2.0 ** -52
+        w.append(np.stack([1000.0 * a, 1.0 * (1 - a), speed * rng.uniform(-1, 1, m), 10 * rng.uniform(-1, 1, m), p * noise, a, 1 - a]))
+    return w
+
+
+@pytest.mark.parametrize("speed", (0.0, 1e-12, 1.0, 2000.0))
+@pytest.mark.parametrize("options", (HLLC, HLL, THORNBER, APC))
+def test_adjoint_face_velocity_is_the_solvers(arith, options, speed):
+    """The adjoint recomputes the face velocity; its last bit decides the side of a
+    face at rest (the volume fraction that rides the contact), so it has to be the
+    solver's own, bit for bit."""
+    wl, wr = interface_faces(20000, 11, speed)
+    _, uf, vjp_uf = faces(arith, options, WATER_AIR, wl, wr)
+    print(f"options {options} speed {speed:g}: {np.mean(uf != vjp_uf):.3f} differ, {np.mean((uf >= 0) != (vjp_uf >= 0)):.4f} on the other side")
+    assert np.array_equal(uf, vjp_uf)
