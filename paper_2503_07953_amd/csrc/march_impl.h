@@ -14,8 +14,9 @@
 // 256^3 in FP64 (two fluids) the two passes moved 428 B per cell and took 668 +
 // 775 us, at the rate of a large copy; this one moves 268 B and takes 1068 us.
 // The FP32 form is bound by its instructions (94 % of the issue rate at two
-// waves per SIMD): 409 + 529 us before, 892 us now.  Rounding is that of the
-// separate passes (FP32: bit for bit).
+// waves per SIMD): 409 + 529 us before, 892 us now.  The FP32 form rounds as
+// the separate passes do, bit for bit; in FP64 the accumulator joins the x axis
+// first.
 //
 // Why this shape: a tile in LDS with y and x halos around it fits twice into a
 // CU, and its load phase then finds too little other work (1.88 ms).  Marching
@@ -120,7 +121,8 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
   const bool out_lane = valid && lane >= 3 && lane <= 60 && xpos >= 0 && xpos < nx;
   const bool xface = valid && lane >= 3 && lane <= 61 && xpos >= 0 && xpos <= nx;
 
-  // SSP-RK3, Shu-Osher form (Sec. 3.4): next state = ka q^n + kb (q_k + dt r)
+  // SSP-RK3, Shu-Osher form (Sec. 3.4): next state = ka q^n + kb (q_k + dt r),
+  // rounded as rk3_stage rounds it (q^n counts as 0 in stage 1)
   double dt = 0.0, ka = 0.0, kb = 1.0;
   if constexpr (kStep) {
     dt = st.dt_ptr ? *st.dt_ptr : st.dt;
@@ -317,9 +319,9 @@ __global__ __launch_bounds__(64, 2) void march_kernel(Params pm, const Real* __r
           r = (NF == 2 && v >= R::ALPHA) ? r + dx[v] : fmaf(ihx, dx[v], r);
         }
         if constexpr (kStep) {
-          // combined in double
+          // combined in double, the fused products written out
           const double ukv = kF64 ? Uc[v] : double(uk[v]);
-          const double out = ka * double(qv[v]) + kb * (ukv + dt * double(r));
+          const double out = fma(ka, double(qv[v]), kb * fma(dt, double(r), ukv));
           if (out_lane) store_at(qout + v * nc + ob, o, Real(out));
         } else {
           if (out_lane) store_at(acc + v * nc + ob, o, r);
