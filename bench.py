@@ -39,8 +39,9 @@ def pass_bytes_per_cell(kind, neq, esize, ndim, stage_mix=(1, 1, 1)):
     writes it, and the x pass, last, reads q_k, acc and (stages 2 and 3) q^n
     and writes the next stage state.  In 1D the x pass is alone: q_k, q^n,
     next state.  The signal reduction reads q once.  Large 3D grids take y and
-    x in one launch, counted as pass_x: it moves the x pass's bytes.  2D grids
-    take both axes in one pass_x launch that has no accumulator to read.
+    x in one launch, counted as pass_x: it moves the x pass's bytes.  In 2D the
+    model is that of two passes, y first and x last; the library takes both axes in
+    one pass_x launch, which has no accumulator to read or write.
     """
     first = {1: "pass_x", 2: "pass_y", 3: "pass_z"}[ndim]
     reads_qn = (0 + 1 + 1) / 3.0
@@ -53,12 +54,14 @@ def pass_bytes_per_cell(kind, neq, esize, ndim, stage_mix=(1, 1, 1)):
     return 3 * neq * esize
 
 
-# Algorithmic FP64 operations per cell for one axis pass of the 3D two-fluid
-# system (counted from the method's formulas): cons->prim 21,
-# WENO5-JS 97 per row x 8 rows, HLLC 106 per face, flux difference and
-# volume-fraction source 30.  The stage update adds 32 per cell on the last pass.
-FLOPS_PASS_3D2F = 21 + 97 * 8 + 106 + 30
-FLOPS_STAGE_UPDATE = 32
+# FP64 operations per cell for one axis pass of the 3D two-fluid system, counted
+# from the formulas in the form that the double kernels evaluate them (a fused
+# multiply-add is one, a reciprocal or inverse root with its refinement four or
+# three): cons->prim 23, WENO5-JS 49 per row x 8 rows, HLLC 84 per face, flux
+# difference and volume-fraction source 20.  The stage update adds 24 per cell on
+# the last pass.
+FLOPS_PASS_3D2F = 23 + 49 * 8 + 84 + 20
+FLOPS_STAGE_UPDATE = 24
 
 
 def time_steps(S, q, steps, warmup, cfl, kernel_steps=None, repeats=1):

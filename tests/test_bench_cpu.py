@@ -60,3 +60,13 @@ def test_committed_counter_summaries_match_the_committed_kernels():
             assert bench.measured_traffic_bytes(kind, prec, n) > 0
     for kind in ("pass_x", "pass_y", "pass_z"):
         assert bench.measured_valu(kind, n) > 0, "profiles/valu_sweep_bubble_cloud_256_fp64.md is stale"
+
+
+def test_counted_operations_are_executed():
+    """The operations that the attainable fractions price are no more than the
+    instructions that the kernels were counted to issue a cell: z is one axis, the
+    marching pass (pass_x) two and the stage update."""
+    n = 256 ** 3
+    issued = {k: bench.measured_valu(k, n) * 64 / n for k in ("pass_z", "pass_x")}
+    assert bench.FLOPS_PASS_3D2F <= issued["pass_z"], issued
+    assert 2 * bench.FLOPS_PASS_3D2F + bench.FLOPS_STAGE_UPDATE <= issued["pass_x"], issued
