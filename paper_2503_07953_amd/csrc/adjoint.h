@@ -57,6 +57,28 @@ __host__ __device__ __forceinline__ void cons_to_prim_vjp(const Params& pm, cons
   }
 }
 
+// The pressure with rho |u|^2/2 taken off rho E first, where cons_to_prim takes Pi
+// off first; W holds the velocities.  WENO's weights at nearly uniform pressure
+// answer to its last bits, and their derivatives to 1e-8 of a gradient: either
+// rounding is as good as the other there, and this is the one that the derivative of
+// the reconstruction of p is taken at, so that gradients do not move with the
+// forward pass' rounding.  The fused products are written out for the same reason.
+template <int NF, int D>
+__host__ __device__ __forceinline__ double pressure_energy_first(const Params& pm, const double* U, const double* W) {
+  using R = Rows<NF, D>;
+  double rho = U[0];
+  if constexpr (NF == 2) rho = U[0] + U[1];
+  double usq = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) usq = fma(W[R::MOM + d], W[R::MOM + d], usq);
+  double Gam, Pi;
+  if constexpr (NF == 2)
+    mixture<NF, double>(pm, U[R::ALPHA], U[R::ALPHA + 1], Gam, Pi);
+  else
+    mixture<NF, double>(pm, 1.0, 0.0, Gam, Pi);
+  return (fma(-0.5 * rho, usq, U[R::E]) - Pi) * fast_rcp(Gam);
+}
+
 // The same from the primitive state W (u and p are at hand; no inversion).
 template <int NF, int D>
 __host__ __device__ __forceinline__ void cons_to_prim_vjp_at_prim(const Params& pm, const double* W, const double* wbar,

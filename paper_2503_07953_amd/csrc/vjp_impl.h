@@ -6,7 +6,8 @@
 // in deterministic passes (no atomics).  A pass over axis DIR does, per wave,
 // for 64 consecutive positions along the axis:
 //   (a) the primitives of the 68 positions that the stencils touch are staged
-//       in LDS (ghosts remapped, one conversion per position);
+//       in LDS (ghosts remapped, one conversion per position, rounded as the
+//       forward passes round it, so that every face takes the forward's side);
 //   (b) WENO at every position's centre (both biased values at once);
 //   (c) at every position's low face the face cotangents Fbar = rbar_f/h_f -
 //       rbar_{f-1}/h_{f-1} and ufbar = sum_j (alpha_j rbar_alpha_j/h)_{f-1} -
@@ -127,6 +128,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
   // primitives by row, line and slot (slot = lane + 2); the rows of rbar, and
   // later of the cell sums, of the y and z axes by row, line and lane
   __shared__ double sw[NEQ * TB * LS];
+  __shared__ double sp[TB * LS];  // the pressure that WENO^T of its row is taken at
   __shared__ double sr[DIR == 0 ? 1 : NEQ * TB * LS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, b = tid >> 6;
@@ -184,6 +186,7 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
     }
     if (flip) U[R::MOM + DIR] = -U[R::MOM + DIR];
     cons_to_prim<NF, D, double>(pm, U, W);
+    sp[bb * LS + s] = pressure_energy_first<NF, D>(pm, U, W);
 #pragma unroll
     for (int v = 0; v < NEQ; ++v) sw[(v * TB + bb) * LS + s] = W[v];
   }
@@ -287,7 +290,8 @@ __global__ __launch_bounds__((VjpTile::NT)) void vjp_axis_kernel(Params pm, VjpG
     const double gR = real_face ? WRb[v] : 0.0;
     const double gL = lane_shift<kFromNext>(real_face ? WLb[v] : 0.0);
     double gD[4];
-    weno_centre_vjp<WV>(Wat(v, 0), Wat(v, 1), Wat(v, 2), Wat(v, 3), Wat(v, 4), K, cf, nst, gL, gR, gD);
+    const double* f = (v == R::E) ? &sp[b * LS + lane] : &sw[(v * TB + b) * LS + lane];
+    weno_centre_vjp<WV>(f[0], f[1], f[2], f[3], f[4], K, cf, nst, gL, gR, gD);
     const double ctr = gL + gR;
     // difference k of the centre c is the edge above position c - 2 + k: the
     // edge above this position collects gD[2] of its own centre, gD[1] and
