@@ -537,26 +537,31 @@ int mfc_set_grid(mfc_ctx* c, int axis, const double* faces) {
     }
     return MFC_OK;
   }
-  // every active axis gets a table (uniform axes: the uniform coefficients)
+  // every active axis gets a table (uniform axes: the uniform coefficients).  All of
+  // them are built and have their memory before the first is replaced: the kernels
+  // read every axis' table once one is set.
+  std::vector<double> tab[3];
   for (int d = 0; d < c->prob.ndim; ++d) {
-    std::vector<double> tab;
-    if (!mfc::build_axis_table(c->pm, d, c->faces[d], c->prob.dx[d], tab)) {
+    if (!mfc::build_axis_table(c->pm, d, c->faces[d], c->prob.dx[d], tab[d])) {
       c->faces[axis] = keep;
       return fail(c, MFC_ERR_ARG, "degenerate grid: a reconstruction system is singular");
     }
-    std::vector<float> tabf(tab.begin(), tab.end());
-    const size_t nb = tab.size();
-    if (!c->nu_d[d]) {
-      if (hipMalloc((void**)&c->nu_d[d], nb * sizeof(double)) != hipSuccess ||
-          hipMalloc((void**)&c->nu_f[d], nb * sizeof(float)) != hipSuccess) {
-        (void)hipGetLastError();
-        c->faces[axis] = keep;
-        return fail(c, MFC_ERR_ALLOC, "grid table allocation failed");
-      }
+  }
+  for (int d = 0; d < c->prob.ndim; ++d) {
+    if ((!c->nu_d[d] && hipMalloc((void**)&c->nu_d[d], tab[d].size() * sizeof(double)) != hipSuccess) ||
+        (!c->nu_f[d] && hipMalloc((void**)&c->nu_f[d], tab[d].size() * sizeof(float)) != hipSuccess)) {
+      (void)hipGetLastError();
+      c->faces[axis] = keep;
+      return fail(c, MFC_ERR_ALLOC, "grid table allocation failed");
     }
-    hipError_t e = hipMemcpy(c->nu_d[d], tab.data(), nb * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->nu_f[d], tabf.data(), nb * sizeof(float), hipMemcpyHostToDevice);
+  }
+  for (int d = 0; d < c->prob.ndim; ++d) {
+    const std::vector<float> tabf(tab[d].begin(), tab[d].end());
+    hipError_t e = hipMemcpy(c->nu_d[d], tab[d].data(), tab[d].size() * sizeof(double), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(c->nu_f[d], tabf.data(), tabf.size() * sizeof(float), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(c, e, "set_grid: copy");
+  }
+  for (int d = 0; d < c->prob.ndim; ++d) {
     c->pm.nu[d] = c->nu_d[d];
     c->pm.nuf[d] = c->nu_f[d];
   }
