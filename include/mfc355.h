@@ -137,7 +137,7 @@ typedef struct {
   double weno_eps;     /* WENO smoothness regularization, 1e-30 <= eps < 1e300
                           (1e-6); smaller values are rejected with MFC_ERR_ARG
                           because the double reconstruction normalizes through
-                          a product of eight terms of size >= 4 eps */
+                          a product of eight terms of size >= 3/4 eps */
   int32_t weno_variant; /* MFC_WENO_JS, MFC_WENO_Z, MFC_TENO or MFC_WENO_M */
   int32_t riemann_solver; /* MFC_HLLC (0) or MFC_HLL */
   int32_t low_mach;       /* MFC_LOW_MACH_NONE (0), _THORNBER or _CHEN_APC (HLLC only) */
@@ -200,7 +200,7 @@ int mfc_step(mfc_ctx* ctx, void* q, double cfl, double dt_fixed, double t_remain
  *   flag_dev  caller's device int (required): set to nonzero when c^2 <= 0 or
  *             a non-finite flux is met, never cleared by the library.
  * Size limit: 3 * round256(neq * ncell * sizeof(element)) + round256(8 *
- * max(8192, blocks of the first axis pass)) + 256 bytes must fit
+ * max(8192, blocks of a 3D grid's first axis pass)) + 256 bytes must fit
  * MFC_STATIC_SCRATCH_BYTES (about 1.3M cells for 3D two-fluid FP64, 2.7M in
  * FP32), else MFC_ERR_SHAPE before any HIP call.  MFC_ERR_HIP if a launch
  * fails or the array's address cannot be resolved.

@@ -142,8 +142,9 @@ int ensure_vjp_scratch(mfc_ctx* c) {
   return MFC_OK;
 }
 
-// Smallest accepted WENO eps: (4 eps)^8 stays far above the smallest normal
-// double (2.2e-308) for every eps >= 1e-30.
+// Smallest accepted WENO eps: the double reconstructions normalize through products
+// of up to eight indicators of at least 3/4 eps each, and (3/4 eps)^8 stays far above
+// the smallest normal double (2.2e-308) for every eps >= 1e-30.
 constexpr double kMinWenoEps = 1e-30;
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -250,7 +251,7 @@ int mfc_validate(const mfc_problem* p) {
   for (int i = 0; i < p->num_fluids; ++i)
     if (!(p->gamma[i] > 1.0) || !(p->pi_inf[i] >= 0.0) || !(p->pi_inf[i] < 1e300)) return MFC_ERR_ARG;
   // the double reconstructions normalize through products of up to eight
-  // smoothness indicators, each at least 4 eps: eps below kMinWenoEps would
+  // smoothness indicators, each at least 3/4 eps: eps below kMinWenoEps would
   // let that product underflow on flat data
   if (!(p->weno_eps >= kMinWenoEps) || !(p->weno_eps < 1e300)) return MFC_ERR_ARG;
   if (p->weno_variant < MFC_WENO_JS || p->weno_variant > MFC_WENO_M) return MFC_ERR_UNSUPPORTED;
@@ -266,7 +267,7 @@ int mfc_validate(const mfc_problem* p) {
 }
 
 // Partials buffer: the fixed-shape reductions (kReduceBlocks per row, up to
-// 8 rows) and the signal maxima of the first axis pass of a CFL step.
+// 8 rows) and the signal maxima of the first axis pass of a 3D CFL step.
 static size_t partial_len(const mfc_problem& p) {
   const long long red = (long long)mfc::kReduceBlocks * 8;
   const long long sig = mfc::signal_partials(p.ndim, p.n);

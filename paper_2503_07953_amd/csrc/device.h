@@ -1007,7 +1007,10 @@ __host__ __device__ __forceinline__ bool hllc_fp32(const Params& pm, const T* WL
 // and (S_R, -S_L, S_L S_R, 1/(S_R - S_L)) otherwise; every row's U and F are
 // formed from the side's primitives as they are used.  Volume fractions take
 // the same formula on alpha u_n, and the face velocity is (a u_L + b u_R) r,
-// so that a uniform alpha stays uniform.  Returns true as hllc does.
+// so that a uniform alpha stays uniform.  Returns true as hllc does.  One form for
+// both precisions: no side hangs on the last bit here, so the FP32 form takes the
+// double sound speed above and the products as fused below, not the order of
+// operations of hllc_fp32 (the same holds for thornber).
 // ---------------------------------------------------------------------------
 template <int NF, int D, int DIR, typename T>
 __host__ __device__ __forceinline__ bool hll(const Params& pm, const T* WL, const T* WR, T* F, T& uf) {

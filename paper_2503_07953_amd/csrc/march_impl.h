@@ -12,11 +12,11 @@
 // What it replaces: a y pass and an x pass that each read q and converted it,
 // and handed the RHS accumulator from one to the other through memory.  At
 // 256^3 in FP64 (two fluids) the two passes moved 428 B per cell and took 668 +
-// 775 us, at the rate of a large copy; this one moves 268 B and takes 1068 us.
-// The FP32 form is bound by its instructions (94 % of the issue rate at two
-// waves per SIMD): 409 + 529 us before, 892 us now.  The FP32 form rounds as
-// the separate passes do, bit for bit; in FP64 the accumulator joins the x axis
-// first.
+// 775 us, at the rate of a large copy; this one moves 268 B and takes 1060 us.
+// The FP32 form takes 915 us instead of 409 + 529: 1849 instructions a cell, for
+// which its two waves per SIMD issue in 60 % of their cycles (FP64: 1463 and 50 %,
+// 28 % waiting for memory).  It rounds as the separate passes do, bit for bit; in
+// FP64 the accumulator joins the x axis first.
 //
 // Why this shape: a tile in LDS with y and x halos around it fits twice into a
 // CU, and its load phase then finds too little other work (1.88 ms).  Marching

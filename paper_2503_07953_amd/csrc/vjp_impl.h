@@ -26,8 +26,8 @@
 // positions of every face (48 doubles a face and axis for two fluids in 3D)
 // and a cell pass that gathered them: 2.3 KB per cell through memory, and the
 // indicators of a centre formed four times.  RHS adjoint, two fluids: 96 x 80 x
-// 72 cells 440 -> 184 us, 128^3 1666 -> 677, 256^2 47.5 -> 28.9, 64^2 25.2 ->
-// 20.4.
+// 72 cells 440 -> 185 us, 128^3 1666 -> 690, 256^2 47.5 -> 28.7, 64^2 25.2 ->
+// 20.2.
 //
 // Lanes 3..60 of a wave are outputs (a cell needs the centres two below to two
 // above it and their faces); a line's positions run from -pad to n + pad - 1,
